@@ -14,11 +14,15 @@
 //     that split every K/V tile between them (each takes KW keys of the
 //     BN = KS*KW-key tile).  The KS waves of a query block keep separate
 //     running (max, sum, output) and are merged through LDS at the end, like
-//     the chunk partials of the sequence-parallel merge.  Two waves per SIMD
-//     let one wave's matrix work overlap another's softmax.  Shapes: 8
-//     waves of 128 rows x 2 splits or 64 rows x 4 splits over 128-key tiles
-//     (d <= 72, one workgroup per CU); 4 waves of 128 rows over 64-key (d
-//     <= 72) or 32-key (d = 128) tiles, two workgroups per CU;
+//     the chunk partials of the sequence-parallel merge.  Two or three waves
+//     per SIMD let one wave's matrix work overlap another's softmax.  Shapes
+//     (chosen by pick_shape below from the counts of query tiles):
+//       wide    8 waves, 128 rows x 2 splits, 128-key (d = 128: 64-key) tiles
+//       narrow  8 waves, 64 rows x 4 splits, 128-key tiles (d <= 72)
+//       quad    4 waves, 128 rows, 64-key (d = 128: 32-key) tiles, two
+//               workgroups per CU
+//       oct     8 waves, 256 rows, 64-key (d = 128: 32-key) tiles (d >= 72)
+//       six     12 waves, 192 rows x 2 splits, 64-key tiles (d <= 72)
 //   * K/V tiles go from memory straight into LDS (buffer loads with an LDS
 //     destination: no registers, no LDS store instructions), NSTAGE tiles
 //     deep, so the loads of the next tiles are in flight while tile t is
@@ -128,8 +132,8 @@ struct Cfg {
     static constexpr int Q_PER_WAVE = (Q_PIECES + NW - 1) / NW;
     // the query tile is staged through LDS where it fits the K and V tiles
     // of stage NSTAGE-1 (rows 0..BN-1 in its K region, the rest in its V
-    // region); otherwise (128 rows of d = 128 over 32-key tiles) each wave
-    // loads its rows straight into registers
+    // region); otherwise (128 rows of d = 128 over 32-key tiles, 192 and 256
+    // rows) each wave loads its rows straight into registers
     static constexpr bool Q_LDS = BM * ROWB <= 2 * TILE_BYTES;
     static constexpr int NKB = KW / 32;              // 32-key blocks of S^T per wave
     static constexpr int NKS = KW / 16;              // 16-key PV steps per wave
@@ -146,9 +150,7 @@ struct Cfg {
     static_assert(!TAIL || (D - TB <= 15 && D - TB > 0 && KW % 32 == 0), "tail block: dims TB..D-1, then the ones row");
     static_assert(KW % 32 == 0, "a wave takes whole 32-key blocks");
     static_assert(TILE_BYTES % 1024 == 0, "tiles are whole 64-lane loads (a query load lies in one region)");
-    static_assert(DMA_PER_TILE >= NW, "every wave loads part of each tile");
-    static_assert(BM * ROWB % 1024 == 0, "the query tile is whole 64-lane loads");
-    static_assert(Q_LDS || DK == D, "query rows loaded into registers have no padding chunk");
+    static_assert(!Q_LDS || BM * ROWB % 1024 == 0, "the query tile is whole 64-lane loads");
     static_assert(LDS_BYTES <= LDS_BUDGET, "LDS budget");
     static_assert(NSTAGE == 4, "the main loop is unrolled over four stages");
 };
@@ -241,10 +243,11 @@ __device__ __forceinline__ void attn_segment(const Args& a, unsigned char* lds, 
             }
         } else {
             // straight into registers, issued before the tile loads (the
-            // prologue's wait for tile 0 covers them)
+            // prologue's wait for tile 0 covers them); chunks past d read zero
 #pragma unroll
             for (int kk = 0; kk < C::KSTEPS; ++kk)
-                qf[kk] = __builtin_bit_cast(bf16x8, bload(rq, (uint32_t)(qb * 32 + c) * rowb + 32 * kk + 16 * hf));
+                qf[kk] = __builtin_bit_cast(
+                    bf16x8, bload(rq, 2 * kk + hf < C::CH ? (uint32_t)(qb * 32 + c) * rowb + 32 * kk + 16 * hf : kOOB));
         }
     }
     // Tile loads: load n of this wave fills LDS chunks 64*ins .. 64*ins+63
@@ -584,7 +587,8 @@ __device__ __forceinline__ void attn_segment(const Args& a, unsigned char* lds, 
     // flight.  A wave issues the same number of loads for every tile (twice
     // as many for a tile that straddles the slice edge, which only makes the
     // wait stricter): 2*DMA_PER_WAVE if it takes one of the leftover 1 KiB
-    // pieces of a tile, 2*(DMA_PER_TILE / NW) otherwise.
+    // pieces of a tile, 2*(DMA_PER_TILE / NW) otherwise (none, for the waves
+    // of a shape with more waves than pieces).
     const bool extra_piece = wave + (C::DMA_PER_WAVE - 1) * C::NW < C::DMA_PER_TILE;
     auto wait_tiles = [&](auto n_c) {
         constexpr int N = decltype(n_c)::value;
@@ -1022,9 +1026,10 @@ __device__ __forceinline__ void attn_segment(const Args& a, unsigned char* lds, 
 // pairs share an XCD; G1 is a multiple of 8, so both groups start on XCD 0.
 // Workgroups of 4 waves (one per SIMD) are built to run two per CU: each
 // wave is then held to 256 registers, so that every SIMD interleaves two
-// waves of independent workgroups, which no barrier keeps in step.
+// waves of independent workgroups, which no barrier keeps in step.  The 12
+// waves of "six" are three per SIMD, held to 168 registers.
 template <int D, int QB, int KS, int KW, bool PATCH, bool PARTS, bool PING>
-__global__ __launch_bounds__(64 * QB * KS, QB * KS == 4 ? 2 : 1) void attn_bf16_kernel(Args a) {
+__global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 ? 2 : QB * KS == 12 ? 3 : 1)) void attn_bf16_kernel(Args a) {
     using C = Cfg<D, QB, KS, KW>;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS_BYTES];
     if constexpr (!PARTS) {
@@ -1293,11 +1298,8 @@ hipError_t launch(const AttnParams& p, hipStream_t s) {
     }
 }
 
-// Shapes of 8-wave workgroup.  "Wide": 128 query rows as 4 query blocks x 2
-// key splits (a 128-key tile at d <= 72, 64 keys at d = 128 for the register
-// and LDS budget).  "Narrow" (d <= 72): 64 query rows x 4 key splits of a
-// 128-key tile, for query counts whose 128-row tiles would leave many of the
-// 256 CUs idle.
+// Workgroup shapes, see the top of this file.
+enum Shape { kAuto = 0, kWide, kNarrow, kQuad, kOct, kSix };
 constexpr int kCUs = 256;
 
 double fill(int64_t blocks) {
@@ -1305,69 +1307,110 @@ double fill(int64_t blocks) {
     return rounds ? (double)blocks / (double)(rounds * kCUs) : 1.0;
 }
 
-// XDIT_ATTN_TILE forces one shape (tuning and tests): "wide", "narrow"
-// (8 waves; both fall back to the default at d = 128) or "quad" (4 waves,
-// 128 rows, 64-key tiles; d <= 72, unpartitioned launches); anything else,
-// or unset, picks by the fill estimate.
-int forced_shape() {
+// XDIT_ATTN_TILE forces one shape (tuning and tests) of unpartitioned
+// launches; where a head dim does not have it, and for anything else, or
+// unset, the library picks.
+Shape forced_shape() {
     const char* e = getenv("XDIT_ATTN_TILE");
-    if (e == nullptr) return 0;
-    if (strcmp(e, "wide") == 0) return 1;
-    if (strcmp(e, "narrow") == 0) return 2;
-    if (strcmp(e, "quad") == 0) return 3;
-    return 0;
+    if (e == nullptr) return kAuto;
+    if (strcmp(e, "wide") == 0) return kWide;
+    if (strcmp(e, "narrow") == 0) return kNarrow;
+    if (strcmp(e, "quad") == 0) return kQuad;
+    if (strcmp(e, "oct") == 0) return kOct;
+    if (strcmp(e, "six") == 0) return kSix;
+    return kAuto;
 }
 
 // XDIT_ATTN_KERNEL selects the decomposition: "w64" (64 query rows per
 // wave, attn_w64.hip, head dim 128), "o2" (workgroups of 4 waves, two per
-// CU), "w32" (the 8-wave workgroups of this file, and at d <= 72 the 4-wave
-// 128-row shape where the grid has more query tiles than CUs) or "pp" (the
-// 8-wave shapes with the two halves in ping-pong).  Unset: o2 at d = 128
-// (the Flux chunk step measured 221 vs 228-236 us), w32 at d <= 72 (o2's
-// 64-row, 64-key shape measured 10-18 % slower there).
-static int attn_kernel_choice(int D) {
+// CU), "w32" (the 8-wave workgroups of this file, and at d <= 72 the shapes
+// pick_shape chooses) or "pp" (the 8-wave shapes with the two halves in
+// ping-pong).  Unset: pick_shape.
+static int attn_kernel_choice() {
     const char* e = getenv("XDIT_ATTN_KERNEL");
     if (e != nullptr && strcmp(e, "w64") == 0) return 64;
     if (e != nullptr && strcmp(e, "o2") == 0) return 2;
     if (e != nullptr && strcmp(e, "w32") == 0) return 32;
     if (e != nullptr && strcmp(e, "pp") == 0) return 3;
-    return D > 96 ? 2 : 32;
+    return 0;
+}
+
+// The shape of an unpartitioned launch.
+//   * No more 128-row query tiles than CUs: the 8-wave shapes.  Two waves of
+//     a SIMD then work on the same rows, where a 4-wave workgroup would be
+//     alone on its CU with one (d = 64, 2 x 24 heads, 512 x 4429: wide 42 us,
+//     quad 46; d = 128, 24 heads, 1024 x 4224: wide 68, quad 88; 512 x 4224:
+//     58 and 75).  At d <= 72 narrow where 128-row tiles would leave many
+//     CUs idle.
+//   * More: the cheapest by a model of the rounds, in units of a 128-key
+//     tile swept by a full round of quads (two per CU):
+//       quad: 1 per tile and full round, 0.58 when at most half of the
+//         places are taken, plus 0.5 per round; a workgroup's prologue and
+//         epilogue mostly run under the other one's sweep;
+//       oct (d >= 72): 0.95 per tile and round of 256, plus 2.9: every K
+//         and V tile is read once for 256 rows instead of 128, but nothing
+//         covers the prologue (d = 128, 24 heads, 2048 x 8192: 208 us, quad
+//         225; 16 heads, 4096 x 4224: 131 and 136; d = 72, 16 heads, 4096 x
+//         4096: 87 and 93).  At d = 64 it is no faster (48 heads, patch of
+//         1097 in 17776 rows: 311 us, quad 309; chunk 17776 x 2222: 584 and
+//         552);
+//       six (d <= 72): 0.84 per tile and round of 256, plus 2.9: between
+//         256 and 384 tiles of 128 rows, quads are two on some CUs and one on
+//         others, while 192-row tiles are one each (d = 64, 2 x 24 heads,
+//         845 x 4429: 67 us, quad 77-81, wide 86; d = 72, 2 x 16 heads,
+//         1500 x 4096: 69, 83 and 90; short sweeps tie: 845 x 500 14.3 and
+//         14.0, 845 x 256 10.4 and 9.3).
+Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
+    const int64_t n = (Nq + 127) / 128 * bh;
+    if (n <= kCUs) {
+        if (D > 96) return kWide;
+        const int64_t narrow = (Nq + 63) / 64 * bh;
+        const double qfill_w = (double)Nq / ((Nq + 127) / 128 * 128.0);
+        const double qfill_n = (double)Nq / ((Nq + 63) / 64 * 64.0);
+        return fill(narrow) * qfill_n > 1.1 * fill(n) * qfill_w ? kNarrow : kWide;
+    }
+    const double T = (double)Nk / 128;
+    const int64_t rem = n % (2 * kCUs);
+    const double quad = (double)(n / (2 * kCUs)) * (T + 0.5) + (rem == 0 ? 0 : rem <= kCUs ? 0.58 * T : T) + 2.0;
+    auto rounds = [&](int64_t rows) { return (double)(((Nq + rows - 1) / rows * bh + kCUs - 1) / kCUs); };
+    const double oct = D < 72 ? quad : rounds(256) * (0.95 * T + 2.9);
+    const double six = D > 96 ? quad : rounds(192) * (0.84 * T + 2.9);
+    if (six < quad && six <= oct) return kSix;
+    return oct < quad ? kOct : kQuad;
 }
 
 template <int D, bool PATCH>
 hipError_t dispatch(const AttnParams& p, hipStream_t s) {
-    if (attn_kernel_choice(D) == 2) {
+    constexpr int KW = D > 96 ? 32 : 64;  // keys per wave and tile, but for narrow and six
+    const int choice = attn_kernel_choice();
+    if (choice == 2) {
         // 128 rows x 32-key tiles at d = 128; 64 rows (2 blocks x 2 key
         // splits of a 64-key tile) at d <= 72, whose partitioned launches
         // keep the 8-wave shape (128-row slots)
         if constexpr (D > 96) return launch<D, 4, 1, 32, PATCH>(p, s);
         else if (p.parts <= 0) return launch<D, 2, 2, 32, PATCH>(p, s);
     }
-    if (attn_kernel_choice(D) == 3) {
-        if constexpr (D > 96) return launch<D, 4, 2, 32, PATCH, true>(p, s);
-        else return launch<D, 4, 2, 64, PATCH, true>(p, s);
+    if (choice == 3) return launch<D, 4, 2, KW, PATCH, true>(p, s);
+    if (p.parts > 0) {
+        // split keys fill the GPU by themselves: 128-row query tiles (the
+        // slots' rows); at d = 128 quads, two per CU, unless the launch has
+        // no more workgroups than CUs
+        if constexpr (D > 96)
+            if (choice == 0 && p.whole + p.parts > kCUs) return launch<D, 4, 1, 32, PATCH>(p, s);
+        return launch<D, 4, 2, KW, PATCH>(p, s);
     }
-    if constexpr (D > 96) {
-        return launch<D, 4, 2, 32, PATCH>(p, s);
-    } else {
-        const int forced = forced_shape();
-        const int64_t bh = (int64_t)p.B * p.H;
-        const int64_t wide = (p.Nq + 127) / 128 * bh, narrow = (p.Nq + 63) / 64 * bh;
-        // More 128-row query tiles than CUs: workgroups of 4 waves (128
-        // rows, one key split, 64-key tiles), two per CU, whose waves
-        // interleave on each SIMD as at d = 128 (cog chunk step 630 -> 543
-        // us, patch step 317 -> 308 us).  With no more tiles than CUs most
-        // CUs would get one such workgroup, one wave per SIMD (sd3 patch
-        // step 44 -> 52 us), and the 8-wave shapes stay.
-        if (p.parts <= 0 && (forced == 3 || (forced == 0 && wide > kCUs))) return launch<D, 4, 1, 64, PATCH>(p, s);
-        // split keys fill the GPU by themselves: 128-row query tiles
-        if (forced == 1 || p.parts > 0) return launch<D, 4, 2, 64, PATCH>(p, s);
-        if (forced == 2) return launch<D, 2, 4, 32, PATCH>(p, s);
-        const double qfill_w = (double)p.Nq / ((p.Nq + 127) / 128 * 128.0);
-        const double qfill_n = (double)p.Nq / ((p.Nq + 63) / 64 * 64.0);
-        if (fill(narrow) * qfill_n > 1.1 * fill(wide) * qfill_w) return launch<D, 2, 4, 32, PATCH>(p, s);
-        return launch<D, 4, 2, 64, PATCH>(p, s);
+    Shape shape = forced_shape();
+    if (D > 96 ? shape == kNarrow || shape == kSix : D < 72 && shape == kOct) shape = kAuto;
+    if (D > 96 && choice == 32) shape = kWide;
+    if (shape == kAuto) shape = pick_shape(D, (int64_t)p.B * p.H, p.Nq, p.Nk);
+    if constexpr (D <= 96) {
+        if (shape == kNarrow) return launch<D, 2, 4, 32, PATCH>(p, s);
+        if (shape == kSix) return launch<D, 6, 2, 32, PATCH>(p, s);
     }
+    if constexpr (D >= 72)
+        if (shape == kOct) return launch<D, 8, 1, KW, PATCH>(p, s);
+    if (shape == kQuad) return launch<D, 4, 1, KW, PATCH>(p, s);
+    return launch<D, 4, 2, KW, PATCH>(p, s);
 }
 
 }  // namespace
@@ -1383,7 +1426,7 @@ hipError_t launch_attn_fixup(const AttnParams& p, int q_tiles, int T, hipStream_
 
 hipError_t launch_attn_bf16(const AttnParams& p, hipStream_t s) {
     const bool patch = p.fresh_k != nullptr;
-    if (p.D == 128 && attn_kernel_choice(p.D) == 64) return launch_attn_w64(p, s);
+    if (p.D == 128 && attn_kernel_choice() == 64) return launch_attn_w64(p, s);
     switch (p.D) {
         case 64: return patch ? dispatch<64, true>(p, s) : dispatch<64, false>(p, s);
         case 72: return patch ? dispatch<72, true>(p, s) : dispatch<72, false>(p, s);

@@ -1,0 +1,80 @@
+"""Parity of the bf16 workgroup shapes of 256 rows ("oct", head dim >= 72)
+and 192 rows ("six", head dim <= 72), forced with XDIT_ATTN_TILE, at the edges of their
+query and key tiles, and of the shapes the library picks by itself on both
+sides of one workgroup per CU, against the fp64 oracle on sampled rows."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2411_01738_amd as xd
+from paper_2411_01738_amd.inputs import random_io, sample_rows
+from tests.gpu_util import check_lse, check_out, to_gpu, to_np, torch_mod
+
+pytestmark = pytest.mark.gpu
+
+FORCED = [("oct", 72), ("oct", 128), ("six", 64), ("six", 72)]
+
+
+def _chunk(torch, orc, B, H, d, nq, nk, what, rows=None):
+    q, k, v = (random_io((B, n, H, d), "bf16", 5000 + n + i) for i, n in enumerate((nq, nk, nk)))
+    out = torch.full((B, nq, H, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    lse = torch.full((B, H, nq), float("nan"), device="cuda", dtype=torch.float32)
+    xd.xdit_chunk_attn(to_gpu(q, "bf16"), to_gpu(k, "bf16"), to_gpu(v, "bf16"), out, lse)
+    rows = np.arange(nq) if rows is None else rows
+    ro, rl = orc.attention(q[:, rows].copy(), k, v)
+    check_out(to_np(out)[:, rows], ro, "bf16", what)
+    check_lse(lse.cpu().numpy()[:, :, rows], rl, "bf16", what + " lse")
+
+
+@pytest.mark.parametrize("shape,d", FORCED)
+def test_chunk_edges(shape, d, monkeypatch):
+    torch, orc = torch_mod(), oracle.get()
+    monkeypatch.setenv("XDIT_ATTN_TILE", shape)
+    rows = 256 if shape == "oct" else 192
+    for nq, nk in [(1, 1), (rows - 1, 63), (rows, 64), (rows + 1, 65), (2 * rows + 33, 645), (40, 0), (97, 130)]:
+        print(f"[shape] {shape} d={d} {nq} x {nk}", flush=True)
+        _chunk(torch, orc, 1, 2, d, nq, nk, f"{shape} d={d} {nq} x {nk}")
+
+
+@pytest.mark.parametrize("shape,d", FORCED)
+def test_patch_and_ring(shape, d, monkeypatch):
+    """Two fresh ranges off the tile edges with queries of their own, the
+    buffer bit for bit; then a ring of two chunks cut inside a tile."""
+    torch, orc = torch_mod(), oracle.get()
+    monkeypatch.setenv("XDIT_ATTN_TILE", shape)
+    B, H, N, nq = 2, 2, 433, 270
+    ranges = [(37, 150), (300, 71)]
+    F = sum(n for _, n in ranges)
+    q = random_io((B, nq, H, d), "bf16", 1)
+    kv = np.ascontiguousarray(random_io((2, B, N, H, d), "bf16", 2))
+    fk, fv = random_io((B, F, H, d), "bf16", 3), random_io((B, F, H, d), "bf16", 4)
+    kvg = to_gpu(kv, "bf16")
+    out = torch.full((B, nq, H, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    lse = torch.full((B, H, nq), float("nan"), device="cuda", dtype=torch.float32)
+    xd.xdit_patch_attn_ranges(to_gpu(q, "bf16"), kvg, ranges, to_gpu(fk, "bf16"), to_gpu(fv, "bf16"), out, lse)
+    base = 0
+    for o, n in ranges:
+        kv[0][:, o:o + n], kv[1][:, o:o + n] = fk[:, base:base + n], fv[:, base:base + n]
+        base += n
+    assert np.array_equal(to_np(kvg), kv)
+    ro, rl = orc.attention(q, kv[0].copy(), kv[1].copy())
+    check_out(to_np(out), ro, "bf16", f"{shape} patch d={d}")
+    check_lse(lse.cpu().numpy(), rl, "bf16", f"{shape} patch lse d={d}")
+    out.fill_(float("nan"))
+    lse.fill_(float("-inf"))
+    for a, b in ((0, 201), (201, N)):
+        xd.xdit_chunk_attn_accum(to_gpu(q, "bf16"), to_gpu(kv[0][:, a:b], "bf16"), to_gpu(kv[1][:, a:b], "bf16"), out, lse)
+    check_out(to_np(out), ro, "bf16", f"{shape} ring d={d}")
+    check_lse(lse.cpu().numpy(), rl, "bf16", f"{shape} ring lse d={d}")
+
+
+@pytest.mark.parametrize("d,H,nq,nk", [(64, 43, 769, 1300), (72, 43, 850, 1300), (72, 43, 1400, 2600), (128, 64, 510, 200),
+                                       (128, 65, 510, 300), (128, 43, 1300, 2600)])
+def test_picked(d, H, nq, nk):
+    """One workgroup per CU or fewer and just above, where the library goes
+    over to 192-row and 256-row tiles."""
+    torch, orc = torch_mod(), oracle.get()
+    print(f"[picked] d={d} H={H} {nq} x {nk}", flush=True)
+    _chunk(torch, orc, 1, H, d, nq, nk, f"d={d} H={H} {nq} x {nk}", sample_rows(nq, 97, [127, 128, 191, 192, 255, 256]))
