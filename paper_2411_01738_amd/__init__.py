@@ -4,7 +4,10 @@ Thin binding over the C ABI of libxdit.so (include/xdit.h): each function
 takes torch tensors that already live on the GPU, checks that they are dense,
 reads their sizes, passes raw device pointers and torch's current stream, and
 raises XditError when the library rejects the call.  All arithmetic runs in
-the library's HIP kernels; there is no host or PyTorch fallback.
+the library's HIP kernels; there is no host or PyTorch fallback.  Calls go
+through _binding (csrc/binding.cpp), which does the same checks in native
+code; a call that it does not take, for one whose arguments are wrong, goes
+through the checks below, which say why.
 
 Layouts: activations [B, N, H, d]; K/V buffer [2, B, N, H, d]; LSE [B, H, Nq]
 float32.  dtypes: bfloat16 or float32 (LSE always float32).
@@ -27,6 +30,30 @@ __all__ = ["xdit_patch_attn", "xdit_patch_attn_ranges", "xdit_chunk_attn",
 def _torch():
     import torch
     return torch
+
+
+_native = None  # the _binding module; False: not built
+
+
+def _load_native():
+    global _native
+    torch = _torch()
+    lib()  # says what is missing if nothing is built
+    try:
+        from . import _binding
+        _binding.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _native = _binding
+    except (ImportError, AttributeError):
+        _native = False
+    return _native
+
+
+def _done(rc) -> bool:
+    """Whether the native path took the call; raises if the library rejected it."""
+    if rc is None:
+        return False
+    check(rc)
+    return True
 
 
 def _dtype_code(t) -> int:
@@ -74,6 +101,9 @@ def xdit_patch_attn(q, kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v,
     [patch_off, patch_off+patch_len) of kv_buf [2,B,N,H,d] (in place), then
     out = attention(q, updated K, updated V) for the patch's queries
     q [B,patch_len,H,d]."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.patch(q, kv_buf, patch_off, patch_len, fresh_k, fresh_v, out)):
+        return
     _dense(kv_buf, "kv_buf", 5)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
@@ -94,6 +124,9 @@ def xdit_patch_attn_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None) -
     ranges [(off, len), ...] of kv_buf [2,B,N,H,d] (range 0's rows first; F =
     sum of the lengths), then out = attention(q, updated K, updated V) for the
     queries q [B,Nq,H,d] and, if given, lse [B,H,Nq] (natural log)."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.patch_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse)):
+        return
     _dense(kv_buf, "kv_buf", 5)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
@@ -143,6 +176,9 @@ def _chunk_args(q, k, v, out, lse):
 def xdit_chunk_attn(q, k, v, out, lse=None) -> None:
     """Chunk attention: out = attention(q, k, v) and, if given,
     lse [B,H,Nq] = log-sum-exp of the scaled scores (natural log)."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.chunk(q, k, v, out, lse, False)):
+        return
     args = _chunk_args(q, k, v, out, lse)
     _use_current_stream()
     check(lib().xdit_chunk_attn(*args))
@@ -169,6 +205,9 @@ def _workspace(ws):
 def xdit_chunk_attn_split(q, k, v, out, lse=None, splits: int = 0, workspace=None) -> None:
     """xdit_chunk_attn with each query tile's keys split `splits` ways (0: the
     library chooses); workspace: a GPU tensor of split_workspace_bytes bytes."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.chunk_split(q, k, v, out, lse, splits, workspace, False)):
+        return
     args = _chunk_args(q, k, v, out, lse)
     wp, wb = _workspace(workspace)
     _use_current_stream()
@@ -187,6 +226,9 @@ def xdit_patch_attn_split(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None, sp
                           workspace=None) -> None:
     """xdit_patch_attn_ranges with the keys split `splits` ways (0: the
     library chooses); workspace as for xdit_chunk_attn_split."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.patch_split(q, kv_buf, ranges, fresh_k, fresh_v, out, lse, splits, workspace)):
+        return
     _dense(kv_buf, "kv_buf", 5)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
@@ -205,6 +247,9 @@ def xdit_patch_attn_split(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None, sp
 def xdit_chunk_attn_accum(q, k, v, out, lse) -> None:
     """Ring step: merge attention(q, k, v) into the running (out, lse) in
     place.  lse = -inf marks an empty running state (out then ignored)."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.chunk(q, k, v, out, lse, True)):
+        return
     if lse is None:
         raise XditError(-1, "the running lse is required")
     args = _chunk_args(q, k, v, out, lse)
@@ -215,6 +260,9 @@ def xdit_chunk_attn_accum(q, k, v, out, lse) -> None:
 def xdit_chunk_attn_accum_split(q, k, v, out, lse, splits: int = 0, workspace=None) -> None:
     """xdit_chunk_attn_accum with each query tile's keys split `splits` ways
     (0: the library chooses); workspace as for xdit_chunk_attn_split."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.chunk_split(q, k, v, out, lse, splits, workspace, True)):
+        return
     if lse is None:
         raise XditError(-1, "the running lse is required")
     args = _chunk_args(q, k, v, out, lse)
@@ -226,6 +274,9 @@ def xdit_chunk_attn_accum_split(q, k, v, out, lse, splits: int = 0, workspace=No
 def xdit_lse_merge(outs, lses, n: int, out, lse_out=None) -> None:
     """Merge n chunk partials (outs[r] [B,Nq,H,d], lses[r] [B,H,Nq] float32)
     into out, and the merged log-sum-exp into lse_out if given."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.merge(outs, lses, n, out, lse_out)):
+        return
     n = int(n)
     if n < 1 or n > len(outs) or n > len(lses):
         raise XditError(-4, f"n = {n} does not match {len(outs)} outs / {len(lses)} lses")
@@ -250,6 +301,9 @@ def xdit_lse_merge(outs, lses, n: int, out, lse_out=None) -> None:
 def xdit_kv_update(kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v) -> None:
     """Copy fresh K/V [B,patch_len,H,d] into rows [patch_off, patch_off+patch_len)
     of kv_buf [2,B,N,H,d], bit for bit."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.update(kv_buf, patch_off, patch_len, fresh_k, fresh_v)):
+        return
     _dense(kv_buf, "kv_buf", 5)
     _dense(fresh_k, "fresh_k", 4)
     _dense(fresh_v, "fresh_v", 4)

@@ -16,6 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIBRARY = os.path.join(HERE, "libxdit.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["xdit_api.cpp", "attn_bf16.hip", "attn_w64.hip", "attn_f32.hip", "merge_update.hip"]
 ARCH = "gfx950"
 
@@ -63,8 +64,30 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_binding() -> str:
+    """Compile the torch binding's call path (host code) against libxdit.so."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = BINDING + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{p}" for p in cpp_extension.include_paths()],
+           f"-isystem{sysconfig.get_paths()['include']}", os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           f"-L{HERE}", "-l:libxdit.so", *[f"-L{p}" for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stdout}{r.stderr}")
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libxdit.so; returns its path."""
+    """Compile every source, link libxdit.so and the binding; returns the
+    library's path."""
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
@@ -75,6 +98,7 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}{r.stderr}")
     os.replace(tmp, LIBRARY)
+    build_binding()
     if verbose:
         print(f"built {LIBRARY}")
     return LIBRARY

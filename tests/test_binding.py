@@ -1,0 +1,110 @@
+"""The native call path takes only what the checks in Python would pass: a
+call it does not take comes back as None, so that the Python path raises what
+it always raised; on the GPU, calls by both paths give the same bytes."""
+from __future__ import annotations
+
+import pytest
+
+import paper_2411_01738_amd as xd
+from paper_2411_01738_amd import XditError
+
+
+def _binding():
+    torch = pytest.importorskip("torch")
+    nat = xd._load_native()
+    assert nat, "paper_2411_01738_amd/_binding.so is not built"
+    return torch, nat
+
+
+def test_declines_what_python_rejects():
+    torch, nat = _binding()
+    q = torch.zeros(1, 4, 2, 64)
+    kv = torch.zeros(2, 1, 8, 2, 64)
+    lse = torch.zeros(1, 2, 4)
+    # host tensors, wrong types of arguments, missing LSE
+    assert nat.chunk(q, q, q, q, lse, False) is None
+    assert nat.chunk(None, q, q, q, None, False) is None
+    assert nat.chunk_split(q, q, q, q, lse, "2", None, False) is None
+    assert nat.patch(q, kv, 0, 4, q, q, q) is None
+    assert nat.patch_ranges(q, kv, [(0, 4)], q, q, q, None) is None
+    assert nat.patch_split(q, kv, [(0, 4)], q, q, q, None, None, None) is None
+    assert nat.merge([q], [lse], 1, q, None) is None
+    assert nat.update(kv, 0, 4, q, q) is None
+    with pytest.raises(TypeError):
+        nat.chunk(q)
+    with pytest.raises(XditError, match="must be a GPU tensor"):
+        xd.xdit_chunk_attn(q, q, q, q, lse)
+
+
+@pytest.mark.gpu
+def test_both_paths_agree(monkeypatch):
+    torch, nat = _binding()
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16)
+    B, N, H, d, n = 2, 300, 2, 72, 70
+    q, k, v, fk, fv = r(B, n, H, d), r(B, N, H, d), r(B, N, H, d), r(B, n, H, d), r(B, n, H, d)
+    kv0 = r(2, B, N, H, d)
+
+    def calls():
+        out = []
+
+        def new():
+            out.append(torch.zeros_like(q))
+            out.append(torch.full((B, H, n), float("-inf"), device="cuda"))
+            return out[-2:]
+
+        kv = kv0.clone()
+        xd.xdit_chunk_attn(q, k, v, *new())
+        xd.xdit_chunk_attn_accum(q, k, v, *new())
+        ws = torch.empty(xd.split_workspace_bytes(q, N, 2), device="cuda", dtype=torch.uint8)
+        xd.xdit_chunk_attn_split(q, k, v, *new(), 2, ws)
+        xd.xdit_chunk_attn_accum_split(q, k, v, *new(), 2, ws)
+        xd.xdit_patch_attn(q, kv, 5, n, fk, fv, new()[0])
+        xd.xdit_patch_attn_ranges(q, kv, [(5, 30), (200, 40)], fk, fv, *new())
+        xd.xdit_patch_attn_split(q, kv, ((5, 30), (200, 40)), fk, fv, *new(), 2, ws)
+        xd.xdit_lse_merge([out[0], out[4]], [out[1], out[5]], 2, *new())
+        xd.xdit_kv_update(kv, 100, n, fk, fv)
+        # and on a stream of its own
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            xd.xdit_chunk_attn(q, k, v, *new())
+        torch.cuda.current_stream().wait_stream(s)
+        torch.cuda.synchronize()
+        return out + [kv]
+
+    fast = calls()
+    monkeypatch.setattr(xd, "_native", False)
+    for a, b in zip(fast, calls()):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_rejections_are_the_same(monkeypatch):
+    torch, nat = _binding()
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    z = lambda *s, dt=torch.bfloat16: torch.zeros(*s, device="cuda", dtype=dt)
+    q, kv, lse = z(1, 4, 2, 64), z(2, 1, 8, 2, 64), z(1, 2, 4, dt=torch.float32)
+    bad = [lambda: xd.xdit_chunk_attn(q, q, z(1, 5, 2, 64), z(1, 4, 2, 64)),
+           lambda: xd.xdit_chunk_attn(q, q, q, q),                                    # out aliases q
+           lambda: xd.xdit_chunk_attn(q.half(), q, q, q),
+           lambda: xd.xdit_chunk_attn(q, q.transpose(1, 2), q, z(1, 4, 2, 64)),
+           lambda: xd.xdit_chunk_attn(q, q, q, z(1, 4, 2, 64), lse[:, :, :3]),
+           lambda: xd.xdit_chunk_attn_accum(q, q, q, z(1, 4, 2, 64), None),
+           lambda: xd.xdit_patch_attn(q, kv, 6, 4, q, q, z(1, 4, 2, 64)),             # past the buffer
+           lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 2), (1, 2)], q, q, z(1, 4, 2, 64)),
+           lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 1), (2, 1), (4, 2)], q, q, z(1, 4, 2, 64)),
+           lambda: xd.xdit_lse_merge([q], [lse], 2, z(1, 4, 2, 64)),
+           lambda: xd.xdit_kv_update(kv, -1, 4, q, q),
+           lambda: xd.xdit_chunk_attn_split(q, kv[0], kv[1], z(1, 4, 2, 64), None, 17)]
+    codes = []
+    for native in (nat, False):
+        monkeypatch.setattr(xd, "_native", native)
+        for f in bad:
+            with pytest.raises(XditError) as e:
+                f()
+            codes.append((e.value.code, str(e.value)))
+    assert codes[:len(bad)] == codes[len(bad):]
