@@ -225,10 +225,20 @@ __global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && KS * D > 320 ? 1 : 2
         int src, row0;
         uint32_t vo, to;
     };
+    // source(), for this wave's 32 rows alone
+    auto v_source = [&](int lo) -> int {
+        if (!PATCH) return 0;
+        const int hi = min(lo + kKT, a.Nk);
+        if (a.off0 <= lo && hi <= a.off0 + a.len0) return 1;
+        if (a.off1 <= lo && hi <= a.off1 + a.len1) return 2;
+        const bool in0 = a.len0 > 0 && lo < a.off0 + a.len0 && a.off0 < hi;
+        const bool in1 = a.len1 > 0 && lo < a.off1 + a.len1 && a.off1 < hi;
+        return in0 || in1 ? 3 : 0;
+    };
     auto v_tile = [&](int t) -> VTile {
         VTile x;
-        x.src = source(t);
         x.row0 = t * C::BN + kh * kKT;  // this wave's first row of the tile
+        x.src = v_source(x.row0);
         const bool buf = x.src == 0 || x.src == 3;
         const int shift = buf ? 0 : (x.src == 1 ? -a.off0 : a.len0 - a.off1);
         x.r = rows_rsrc(buf ? vbase : fvbase, x.row0 + shift, buf ? a.Nk : (x.src == 1 ? a.len0 : F));
@@ -413,6 +423,33 @@ __global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && KS * D > 320 ? 1 : 2
     const int mine = first_key(ntiles - 1) < a.Nk ? ntiles : ntiles - 1;
     if (ntiles > 0) load_k(0, 0);
     if (ntiles > 1) load_k(1, 1);
+    // Patch: this workgroup's share of the fresh rows goes into the buffer
+    // while the first tiles load (nothing here reads the buffer's fresh rows;
+    // after the sweep the copy had cost a 64-row patch 2 of 12 us).
+    if constexpr (PATCH) {
+        constexpr int CU = 4;  // 16-byte chunks per lane and batch
+        const int r0 = (int)((int64_t)F * qt / a.q_tiles), r1 = (int)((int64_t)F * (qt + 1) / a.q_tiles);
+        const int n = (r1 - r0) * C::CH;
+        float* wk = a.wk + (kbase - a.k);
+        float* wv = a.wv + (vbase - a.v);
+        for (int e0 = tid; e0 < n; e0 += CU * C::THREADS) {
+            f32x4 ck[CU], cv[CU];
+            int64_t to[CU];
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                const int e = min(e0 + u * C::THREADS, n - 1);  // past the share: its last chunk again
+                const int fr = r0 + e / C::CH, cc = 4 * (e % C::CH);
+                to[u] = (int64_t)(fr < a.len0 ? a.off0 + fr : a.off1 + fr - a.len0) * rs + cc;
+                ck[u] = *(const f32x4*)(fkbase + (int64_t)fr * rs + cc);
+                cv[u] = *(const f32x4*)(fvbase + (int64_t)fr * rs + cc);
+            }
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                *(f32x4*)(wk + to[u]) = ck[u];
+                *(f32x4*)(wv + to[u]) = cv[u];
+            }
+        }
+    }
     meet();
     if (mine > 0) {
         phase(0, sc, sc, T_{}, F_{}, [](auto) {});
@@ -422,20 +459,6 @@ __global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && KS * D > 320 ? 1 : 2
     for (int t = 0; t + 1 < mine; ++t) iteration(t, T_{});
     if (mine > 0) iteration(mine - 1, F_{});
     if (mine < ntiles) meet();
-
-    // Patch: this workgroup's share of the fresh rows goes into the buffer
-    // (nothing here reads the buffer's fresh rows).
-    if constexpr (PATCH) {
-        const int r0 = (int)((int64_t)F * qt / a.q_tiles), r1 = (int)((int64_t)F * (qt + 1) / a.q_tiles);
-        float* wk = a.wk + (kbase - a.k);
-        float* wv = a.wv + (vbase - a.v);
-        for (int e = tid; e < (r1 - r0) * C::CH; e += C::THREADS) {
-            const int fr = r0 + e / C::CH, cc = 4 * (e % C::CH);
-            const int j = fr < a.len0 ? a.off0 + fr : a.off1 + fr - a.len0;
-            *(f32x4*)(wk + (int64_t)j * rs + cc) = *(const f32x4*)(fkbase + (int64_t)fr * rs + cc);
-            *(f32x4*)(wv + (int64_t)j * rs + cc) = *(const f32x4*)(fvbase + (int64_t)fr * rs + cc);
-        }
-    }
 
     // Merge of the KS partial sweeps: every wave of a query block takes a
     // share of the output groups.  xs is read only after every wave wrote.
