@@ -23,6 +23,8 @@
 //               workgroups per CU
 //       oct     8 waves, 256 rows, 64-key (d = 128: 32-key) tiles (d >= 72)
 //       six     12 waves, 192 rows x 2 splits, 64-key tiles (d <= 72)
+//       strip   4 waves, 32 rows x 4 splits over 128-key tiles (d = 128: 64
+//               rows x 2 splits over 64-key tiles), one workgroup per CU
 //   * K/V tiles go from memory straight into LDS (buffer loads with an LDS
 //     destination: no registers, no LDS store instructions), NSTAGE tiles
 //     deep, so the loads of the next tiles are in flight while tile t is
@@ -121,8 +123,9 @@ struct Cfg {
     static constexpr int STAGE_BYTES = 2 * REGION;
     // Iteration t reads V of tile t and K of tile t+1 while the tiles after
     // them load: three stages at least, four where they fit (in half the
-    // LDS for workgroups of 4 waves, which run two per CU).
-    static constexpr int LDS_BUDGET = NW == 4 ? kLdsBytes / 2 : kLdsBytes;
+    // LDS for the workgroups of 4 waves that run two per CU).
+    static constexpr bool TWO_PER_CU = NW == 4 && (KS == 1 || (QB == 2 && D <= 72));
+    static constexpr int LDS_BUDGET = TWO_PER_CU ? kLdsBytes / 2 : kLdsBytes;
     static constexpr int NSTAGE = LDS_BUDGET / STAGE_BYTES >= 4 ? 4 : 3;
     static constexpr int VBASE = NSTAGE * REGION;     // the first V region
     static constexpr int DMA_PER_TILE = TILE_BYTES / 1024;  // 64 lanes x 16 bytes per load
@@ -132,9 +135,10 @@ struct Cfg {
     static constexpr int Q_PER_WAVE = (Q_PIECES + NW - 1) / NW;
     // the query tile is staged through LDS where it fits the K and V tiles
     // of stage NSTAGE-1 (rows 0..BN-1 in its K region, the rest in its V
-    // region); otherwise (128 rows of d = 128 over 32-key tiles, 192 and 256
-    // rows) each wave loads its rows straight into registers
-    static constexpr bool Q_LDS = BM * ROWB <= 2 * TILE_BYTES;
+    // region) and is a whole number of 64-lane loads; otherwise (128 rows of
+    // d = 128 over 32-key tiles, 192 and 256 rows, 32 rows of d = 72) each
+    // wave loads its rows straight into registers
+    static constexpr bool Q_LDS = BM * ROWB <= 2 * TILE_BYTES && BM * ROWB % 1024 == 0;
     static constexpr int NKB = KW / 32;              // 32-key blocks of S^T per wave
     static constexpr int NKS = KW / 16;              // 16-key PV steps per wave
     static constexpr bool SUM_BY_MFMA = TAIL;        // a padding row of V^T holds ones
@@ -150,7 +154,6 @@ struct Cfg {
     static_assert(!TAIL || (D - TB <= 15 && D - TB > 0 && KW % 32 == 0), "tail block: dims TB..D-1, then the ones row");
     static_assert(KW % 32 == 0, "a wave takes whole 32-key blocks");
     static_assert(TILE_BYTES % 1024 == 0, "tiles are whole 64-lane loads (a query load lies in one region)");
-    static_assert(!Q_LDS || BM * ROWB % 1024 == 0, "the query tile is whole 64-lane loads");
     static_assert(LDS_BYTES <= LDS_BUDGET, "LDS budget");
     static_assert(NSTAGE == 4, "the main loop is unrolled over four stages");
 };
@@ -1024,12 +1027,13 @@ __device__ __forceinline__ void attn_segment(const Args& a, unsigned char* lds, 
 // whole), or a partitioned launch (PARTS = true, see Args).  Workgroup ids
 // are remapped per group (whole sweeps, cut ranges) so that neighbouring
 // pairs share an XCD; G1 is a multiple of 8, so both groups start on XCD 0.
-// Workgroups of 4 waves (one per SIMD) are built to run two per CU: each
+// Workgroups of 4 waves (one per SIMD; but for strip, which has the CU to
+// itself) are built to run two per CU: each
 // wave is then held to 256 registers, so that every SIMD interleaves two
 // waves of independent workgroups, which no barrier keeps in step.  The 12
 // waves of "six" are three per SIMD, held to 168 registers.
 template <int D, int QB, int KS, int KW, bool PATCH, bool PARTS, bool PING>
-__global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 ? 2 : QB * KS == 12 ? 3 : 1)) void attn_bf16_kernel(Args a) {
+__global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && (KS == 1 || (QB == 2 && D <= 72)) ? 2 : QB * KS == 12 ? 3 : 1)) void attn_bf16_kernel(Args a) {
     using C = Cfg<D, QB, KS, KW>;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS_BYTES];
     if constexpr (!PARTS) {
@@ -1299,7 +1303,7 @@ hipError_t launch(const AttnParams& p, hipStream_t s) {
 }
 
 // Workgroup shapes, see the top of this file.
-enum Shape { kAuto = 0, kWide, kNarrow, kQuad, kOct, kSix };
+enum Shape { kAuto = 0, kWide, kNarrow, kQuad, kOct, kSix, kStrip };
 constexpr int kCUs = 256;
 
 double fill(int64_t blocks) {
@@ -1318,6 +1322,7 @@ Shape forced_shape() {
     if (strcmp(e, "quad") == 0) return kQuad;
     if (strcmp(e, "oct") == 0) return kOct;
     if (strcmp(e, "six") == 0) return kSix;
+    if (strcmp(e, "strip") == 0) return kStrip;
     return kAuto;
 }
 
@@ -1341,7 +1346,12 @@ static int attn_kernel_choice() {
 //     alone on its CU with one (d = 64, 2 x 24 heads, 512 x 4429: wide 42 us,
 //     quad 46; d = 128, 24 heads, 1024 x 4224: wide 68, quad 88; 512 x 4224:
 //     58 and 75).  At d <= 72 narrow where 128-row tiles would leave many
-//     CUs idle.
+//     CUs idle.  Where even the smallest tiles (strip) are no more than the
+//     CUs: strip, since a CU then has a tile's latency to wait for and the
+//     shortest chain of a wave wins (d = 64, 24 heads, 300 x 4429: strip 24.5
+//     us, narrow 27.5; 16 x 2500: 15.1 and 17.0; d = 72, 2 x 16 heads, 256 x
+//     4096: 29.2 and 30.0; d = 128, 24 heads, 200 x 4224: strip 46.8, wide
+//     58.5; 100 x 500, 12 heads: 10.0 and 12.4).
 //   * More: the cheapest by a model of the rounds, in units of a 128-key
 //     tile swept by a full round of quads (two per CU):
 //       quad: 1 per tile and full round, 0.58 when at most half of the
@@ -1362,6 +1372,8 @@ static int attn_kernel_choice() {
 //         14.0, 845 x 256 10.4 and 9.3).
 Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
     const int64_t n = (Nq + 127) / 128 * bh;
+    const int64_t strip_rows = D > 96 ? 64 : 32;
+    if ((Nq + strip_rows - 1) / strip_rows * bh <= kCUs) return kStrip;
     if (n <= kCUs) {
         if (D > 96) return kWide;
         const int64_t narrow = (Nq + 63) / 64 * bh;
@@ -1406,6 +1418,9 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
     if constexpr (D <= 96) {
         if (shape == kNarrow) return launch<D, 2, 4, 32, PATCH>(p, s);
         if (shape == kSix) return launch<D, 6, 2, 32, PATCH>(p, s);
+        if (shape == kStrip) return launch<D, 1, 4, 32, PATCH>(p, s);
+    } else {
+        if (shape == kStrip) return launch<D, 2, 2, 32, PATCH>(p, s);
     }
     if constexpr (D >= 72)
         if (shape == kOct) return launch<D, 8, 1, KW, PATCH>(p, s);

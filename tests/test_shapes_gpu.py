@@ -1,5 +1,5 @@
-"""Parity of the bf16 workgroup shapes of 256 rows ("oct", head dim >= 72)
-and 192 rows ("six", head dim <= 72), forced with XDIT_ATTN_TILE, at the edges of their
+"""Parity of the bf16 workgroup shapes of 256 rows ("oct", head dim >= 72),
+192 rows ("six", head dim <= 72) and 32 or 64 rows ("strip"), forced with XDIT_ATTN_TILE, at the edges of their
 query and key tiles, and of the shapes the library picks by itself on both
 sides of one workgroup per CU, against the fp64 oracle on sampled rows."""
 from __future__ import annotations
@@ -14,7 +14,7 @@ from tests.gpu_util import check_lse, check_out, to_gpu, to_np, torch_mod
 
 pytestmark = pytest.mark.gpu
 
-FORCED = [("oct", 72), ("oct", 128), ("six", 64), ("six", 72)]
+FORCED = [("oct", 72), ("oct", 128), ("six", 64), ("six", 72), ("strip", 64), ("strip", 72), ("strip", 128)]
 
 
 def _chunk(torch, orc, B, H, d, nq, nk, what, rows=None):
@@ -32,7 +32,7 @@ def _chunk(torch, orc, B, H, d, nq, nk, what, rows=None):
 def test_chunk_edges(shape, d, monkeypatch):
     torch, orc = torch_mod(), oracle.get()
     monkeypatch.setenv("XDIT_ATTN_TILE", shape)
-    rows = 256 if shape == "oct" else 192
+    rows = {"oct": 256, "six": 192, "strip": 64 if d == 128 else 32}[shape]
     for nq, nk in [(1, 1), (rows - 1, 63), (rows, 64), (rows + 1, 65), (2 * rows + 33, 645), (40, 0), (97, 130)]:
         print(f"[shape] {shape} d={d} {nq} x {nk}", flush=True)
         _chunk(torch, orc, 1, 2, d, nq, nk, f"{shape} d={d} {nq} x {nk}")
@@ -70,7 +70,8 @@ def test_patch_and_ring(shape, d, monkeypatch):
     check_lse(lse.cpu().numpy(), rl, "bf16", f"{shape} ring lse d={d}")
 
 
-@pytest.mark.parametrize("d,H,nq,nk", [(64, 43, 769, 1300), (72, 43, 850, 1300), (72, 43, 1400, 2600), (128, 64, 510, 200),
+@pytest.mark.parametrize("d,H,nq,nk", [(64, 43, 769, 1300), (72, 43, 850, 1300), (72, 43, 1400, 2600), (128, 64, 510, 200), (64, 8, 1024, 700),
+                                       (64, 8, 1025, 700), (128, 64, 256, 300), (128, 65, 256, 300),
                                        (128, 65, 510, 300), (128, 43, 1300, 2600)])
 def test_picked(d, H, nq, nk):
     """One workgroup per CU or fewer and just above, where the library goes
