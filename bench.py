@@ -40,7 +40,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak (published)
-PEAK_F32_TFLOPS = 157.3     # MI355X fp32 vector peak (published)
+PEAK_F32_TFLOPS = 157.3     # MI355X fp32 vector and matrix peak (published)
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E (published)
 
 # HBM traffic per call of the dominant kernel, in bytes: rocprofv3 --pmc
@@ -431,8 +431,8 @@ def measure(w, t, steps: int, warmup: int, split: bool, extra_timings: bool = Tr
     if dd["flops"]:
         per_launch = dd["flops"] / dd["launches"]
         achieved = per_launch / avg_s / 1e12
-        # bf16 attention runs on the matrix cores; the f32 path is plain VALU code
-        roof = {"kernel": dom, "bound": "mfma" if w.dtype == "bf16" else "alu",
+        # attention runs on the matrix cores at both data types
+        roof = {"kernel": dom, "bound": "mfma",
                 "achieved": round(achieved, 2), "peak": peak,
                 "unit": "TFLOP/s", "frac": round(achieved / peak, 4)}
     else:
