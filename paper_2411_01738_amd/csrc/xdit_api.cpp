@@ -161,15 +161,24 @@ static int64_t part_ws_bytes(const Partition& pt, int64_t pairs, int64_t head_di
 //     cut into s = min(16, 256 / r) parts, so that the last round is full
 //     (K/V reuse among the query tiles of one head is kept in the rounds of
 //     whole sweeps).
-// A partition is taken only when the model saves at least 10 %.  The model
-// counts rounds of one workgroup per CU; at d = 128 the kernel runs two
-// 4-wave workgroups per CU, for which flux's measured alternatives (whole
+// A partition is taken only when the model saves at least 10 % of these.
+// Unpartitioned launches at d <= 72 of more query tiles than CUs also run
+// 192-row tiles (pick_shape in attn_bf16.hip), one workgroup per CU and
+// round, at 1.4 t + 5 (d = 64) or 1.2 t + 6.4 (d = 72) of the same units; no
+// partition is taken where those are ahead.  Measured, us cut / uncut: d = 64,
+// 2 x 24 heads, 700 x 2000 36 / 31; 12 heads, 3300 x 5000 69 / 66; 24 heads,
+// 1738 x 6941 98 / 95; d = 72, 2 x 16 heads, 1100 x 4096 64 / 59; 8 heads,
+// 4400 x 6000 85 / 80.  Beyond the line: d = 64, 24 heads, 1500 x 14000 153 /
+// 172; 48 heads, 770 x 17776 222 / 229; d = 72, 16 heads, 2234 x 12279 157 / 159.
+// The model counts rounds of one workgroup per CU; at d = 128 the kernel runs
+// two 4-wave workgroups per CU, for which flux's measured alternatives (whole
 // rounds of 512 with the rest cut, 512 equal ranges) were no faster than
 // this choice.
 // XDIT_PARTITION=balanced instead cuts the whole launch into 256 equal
 // ranges (ranges cross query tiles; it loses the K/V reuse, so it is never
 // chosen; tests use it), XDIT_PARTITION=none forces no partition.
-static Partition pick_parts(int64_t pairs, int64_t kv_len, int64_t head_dim) {
+static Partition pick_parts(int64_t bh, int64_t q_len, int64_t kv_len, int64_t head_dim) {
+    const int64_t pairs = part_pairs(bh, q_len, 1);
     Partition none;
     const char* force = getenv("XDIT_PARTITION");
     if (force && strcmp(force, "none") == 0) return none;
@@ -211,6 +220,10 @@ static Partition pick_parts(int64_t pairs, int64_t kv_len, int64_t head_dim) {
             pick.parts = r * s;
         }
     }
+    if (head_dim <= 72 && pairs > kCUs) {
+        const double sweep = head_dim < 72 ? 1.4 * t + 5.0 : 1.2 * t + 6.4;
+        if (rounds((q_len + 191) / 192 * bh) * sweep < best) return none;
+    }
     return best < 0.9 * plain ? pick : none;
 }
 
@@ -218,12 +231,14 @@ static Partition pick_parts(int64_t pairs, int64_t kv_len, int64_t head_dim) {
 // sweeps of at most one K/V tile (nothing to cut: a part would sweep its
 // query tile whole), every sweep in `splits` even parts for splits > 1, the
 // library's choice for splits <= 0.
-static Partition call_parts(int32_t dtype, int64_t pairs, int64_t kv_len, int64_t head_dim, int32_t splits) {
+static Partition call_parts(int32_t dtype, int64_t bh, int64_t q_len, int64_t kv_len, int64_t head_dim,
+                            int32_t splits) {
     Partition pt;
+    const int64_t pairs = part_pairs(bh, q_len, 1);
     const int64_t bn = head_dim > 96 ? 64 : 128;  // kernel K/V tile of a partitioned launch
     if (dtype != XDIT_BF16 || pairs == 0 || kv_len <= bn) return pt;
     if (splits > 1) pt.parts = pairs * splits;
-    else if (splits <= 0) pt = pick_parts(pairs, kv_len, head_dim);
+    else if (splits <= 0) pt = pick_parts(bh, q_len, kv_len, head_dim);
     return pt;
 }
 
@@ -234,7 +249,7 @@ static int resolve_parts(const char* fn, const SplitArgs& sa, int32_t dtype, int
     if (sa.splits > XDIT_MAX_SPLITS)
         return fail(XDIT_ERR_RANGE, "%s: splits = %d above %d", fn, sa.splits, XDIT_MAX_SPLITS);
     const int64_t pairs = part_pairs(batch, q_len, heads);
-    const Partition pt = call_parts(dtype, pairs, kv_len, head_dim, sa.splits);
+    const Partition pt = call_parts(dtype, batch * heads, q_len, kv_len, head_dim, sa.splits);
     if (pt.parts > 0) {
         const int64_t need = part_ws_bytes(pt, pairs, head_dim);
         if (sa.workspace == nullptr || sa.workspace_bytes < need)
@@ -477,7 +492,7 @@ int64_t xdit_split_workspace_bytes(int64_t batch, int64_t q_len, int64_t kv_len,
     if (check_dims("xdit_split_workspace_bytes", batch, q_len, kv_len, heads) != XDIT_OK) return -1;
     if (splits > XDIT_MAX_SPLITS) return -1;
     const int64_t pairs = part_pairs(batch, q_len, heads);
-    return part_ws_bytes(call_parts(dtype, pairs, kv_len, head_dim, splits), pairs, head_dim);
+    return part_ws_bytes(call_parts(dtype, batch * heads, q_len, kv_len, head_dim, splits), pairs, head_dim);
 }
 
 int xdit_chunk_attn_split(const void* q, const void* k, const void* v, void* out, float* lse,
@@ -547,7 +562,8 @@ int xdit_chunk_attn_split_noalloc(const void* q, const void* k, const void* v, v
     if (splits > XDIT_MAX_SPLITS)
         return fail(XDIT_ERR_RANGE, "%s: splits = %d above %d", fn, splits, XDIT_MAX_SPLITS);
     const int64_t pairs = part_pairs(batch, q_len, heads);
-    const int64_t need = part_ws_bytes(call_parts(dtype, pairs, kv_len, head_dim, splits), pairs, head_dim);
+    const int64_t need =
+        part_ws_bytes(call_parts(dtype, batch * heads, q_len, kv_len, head_dim, splits), pairs, head_dim);
     if (need > kScratchBytes)
         return fail(XDIT_ERR_RANGE, "%s: the partition needs %lld bytes of scratch, above the %lld-byte maximum",
                     fn, (long long)need, (long long)kScratchBytes);

@@ -226,6 +226,20 @@ def test_split_workspace_bytes():
 
 
 @needs_no_gpu
+@pytest.mark.parametrize("B,nq,nk,H,d,parts", [
+    (2, 845, 4429, 24, 64, 0), (2, 700, 2000, 24, 64, 0), (2, 1100, 4096, 16, 72, 0),   # 192-row tiles, one round
+    (1, 2048, 4096, 17, 64, 256), (1, 1500, 14000, 24, 64, 256), (1, 2234, 12279, 16, 72, 256),  # long sweeps
+    (2, 700, 4000, 48, 64, 256),                                                        # two rounds either way
+    (1, 4224, 4224, 24, 128, 240)])                                                     # no such tiles at 128
+def test_chosen_partition_of_a_few_tiles_over(B, nq, nk, H, d, parts):
+    """A few 128-row query tiles more than the CUs: left whole where 192-row
+    tiles take one round and the sweep is short, the tiles over cut otherwise."""
+    lib = _lib.lib()
+    slot = 128 * (d + 1) * 4
+    assert lib.xdit_split_workspace_bytes(B, nq, nk, H, d, 0, 0) == parts * slot
+
+
+@needs_no_gpu
 def test_split_rejections():
     lib = _lib.lib()
     need = lib.xdit_split_workspace_bytes(1, 16, 1024, 2, 64, 0, 4)
