@@ -119,14 +119,7 @@ def xdit_patch_attn(q, kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v,
                                 _dtype_code(kv_buf)))
 
 
-def xdit_patch_attn_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None) -> None:
-    """General patch step: write fresh_k/fresh_v [B, F, H, d] into the row
-    ranges [(off, len), ...] of kv_buf [2,B,N,H,d] (range 0's rows first; F =
-    sum of the lengths), then out = attention(q, updated K, updated V) for the
-    queries q [B,Nq,H,d] and, if given, lse [B,H,Nq] (natural log)."""
-    nat = _native if _native is not None else _load_native()
-    if nat and _done(nat.patch_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse)):
-        return
+def _patch_args(q, kv_buf, ranges, fresh_k, fresh_v, out, lse):
     _dense(kv_buf, "kv_buf", 5)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
@@ -137,6 +130,10 @@ def xdit_patch_attn_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None) -
     Nq = q.shape[1]
     for t, n, rows in ((q, "q", Nq), (out, "out", Nq), (fresh_k, "fresh_k", F),
                        (fresh_v, "fresh_v", F)):
+        if t is None:
+            if B * rows * H * d > 0:
+                raise XditError(-1, f"{n} is required")
+            continue
         if tuple(t.shape) != (B, rows, H, d):
             raise XditError(-3, f"{n} has shape {tuple(t.shape)}, expected {(B, rows, H, d)}")
         if t.dtype != kv_buf.dtype:
@@ -147,10 +144,21 @@ def xdit_patch_attn_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None) -
             raise XditError(-3, f"lse must be float32 [B,H,Nq] = {(B, H, Nq)}")
     offs = (ctypes.c_int64 * max(nr, 1))(*[int(r[0]) for r in ranges])
     lens = (ctypes.c_int64 * max(nr, 1))(*[int(r[1]) for r in ranges])
+    return ((_ptr(q), Nq, _ptr(kv_buf), nr, offs, lens, _ptr(fresh_k), _ptr(fresh_v), _ptr(out), _ptr(lse)),
+            (B, N, H, d, _dtype_code(kv_buf)))
+
+
+def xdit_patch_attn_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None) -> None:
+    """General patch step: write fresh_k/fresh_v [B, F, H, d] into the row
+    ranges [(off, len), ...] of kv_buf [2,B,N,H,d] (range 0's rows first; F =
+    sum of the lengths), then out = attention(q, updated K, updated V) for the
+    queries q [B,Nq,H,d] and, if given, lse [B,H,Nq] (natural log)."""
+    nat = _native if _native is not None else _load_native()
+    if nat and _done(nat.patch_ranges(q, kv_buf, ranges, fresh_k, fresh_v, out, lse)):
+        return
+    tensors, sizes = _patch_args(q, kv_buf, ranges, fresh_k, fresh_v, out, lse)
     _use_current_stream()
-    check(lib().xdit_patch_attn_ranges(_ptr(q), Nq, _ptr(kv_buf), nr, offs, lens, _ptr(fresh_k),
-                                       _ptr(fresh_v), _ptr(out), _ptr(lse), B, N, H, d,
-                                       _dtype_code(kv_buf)))
+    check(lib().xdit_patch_attn_ranges(*tensors, *sizes))
 
 
 def _chunk_args(q, k, v, out, lse):
@@ -229,19 +237,10 @@ def xdit_patch_attn_split(q, kv_buf, ranges, fresh_k, fresh_v, out, lse=None, sp
     nat = _native if _native is not None else _load_native()
     if nat and _done(nat.patch_split(q, kv_buf, ranges, fresh_k, fresh_v, out, lse, splits, workspace)):
         return
-    _dense(kv_buf, "kv_buf", 5)
-    for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
-        _dense(t, n, 4)
-    _dense(lse, "lse", 3)
-    _, B, N, H, d = kv_buf.shape
-    nr = len(ranges)
-    offs = (ctypes.c_int64 * max(nr, 1))(*[int(r[0]) for r in ranges])
-    lens = (ctypes.c_int64 * max(nr, 1))(*[int(r[1]) for r in ranges])
+    tensors, sizes = _patch_args(q, kv_buf, ranges, fresh_k, fresh_v, out, lse)
     wp, wb = _workspace(workspace)
     _use_current_stream()
-    check(lib().xdit_patch_attn_split(_ptr(q), q.shape[1], _ptr(kv_buf), nr, offs, lens,
-                                      _ptr(fresh_k), _ptr(fresh_v), _ptr(out), _ptr(lse),
-                                      int(splits), wp, wb, B, N, H, d, _dtype_code(kv_buf)))
+    check(lib().xdit_patch_attn_split(*tensors, int(splits), wp, wb, *sizes))
 
 
 def xdit_chunk_attn_accum(q, k, v, out, lse) -> None:

@@ -36,6 +36,61 @@ def test_declines_what_python_rejects():
         xd.xdit_chunk_attn(q, q, q, q, lse)
 
 
+class _GpuTensor:
+    """A host tensor that calls itself a GPU tensor: the checks in Python take
+    it, and no call may get past them to the library."""
+
+    is_cuda = True
+
+    def __init__(self, x):
+        self._x = x
+
+    def __getattr__(self, name):
+        return getattr(self._x, name)
+
+
+@pytest.fixture
+def checks_only(monkeypatch):
+    """The Python checks alone: no native path, and a library that is never
+    to be reached.  Returns a maker of tensors."""
+    torch = pytest.importorskip("torch")
+
+    class Library:
+        def __getattr__(self, name):
+            def launched(*args):
+                raise AssertionError(f"{name} was launched")
+            return launched
+
+    monkeypatch.setattr(xd, "_native", False)
+    monkeypatch.setattr(xd, "lib", lambda: Library())
+    monkeypatch.setattr(xd, "_use_current_stream", lambda: None)
+    return lambda *s, dt=torch.bfloat16: _GpuTensor(torch.zeros(*s, dtype=dt))
+
+
+@pytest.mark.parametrize("call", ["ranges", "split"])
+def test_patch_forms_check_shapes_and_types(checks_only, call):
+    """Sizes that the library cannot see (it takes pointers): a call that
+    passes them on would read or write past the tensors."""
+    import torch
+
+    t, f32 = checks_only, torch.float32
+    B, N, H, d, nq = 1, 8, 2, 64, 6
+    f = xd.xdit_patch_attn_ranges if call == "ranges" else xd.xdit_patch_attn_split
+    good = dict(q=t(B, nq, H, d), kv_buf=t(2, B, N, H, d), ranges=[(0, 3), (5, 2)], fresh_k=t(B, 5, H, d),
+                fresh_v=t(B, 5, H, d), out=t(B, nq, H, d), lse=t(B, H, nq, dt=f32))
+    with pytest.raises(AssertionError, match="was launched"):
+        f(**good)
+    for bad in (dict(out=t(B, nq - 1, H, d)), dict(out=t(B, nq, H, d, dt=f32)), dict(q=t(B, nq, H, 72)),
+                dict(q=t(2, nq, H, d)), dict(q=t(B, nq, H, d, dt=f32)), dict(fresh_k=t(B, 4, H, d)),
+                dict(fresh_v=t(B, 4, H, d)), dict(fresh_v=t(B, 5, H, d, dt=f32)), dict(kv_buf=t(2, B, N, H, d, dt=f32)),
+                dict(lse=t(B, H, nq - 1, dt=f32)), dict(lse=t(B, H, nq)), dict(ranges=[(0, 4), (5, 2)]),
+                dict(out=None), dict(fresh_k=None)):
+        with pytest.raises(XditError):
+            f(**{**good, **bad})
+    with pytest.raises(AssertionError, match="was launched"):  # no fresh rows, none given
+        f(**{**good, "ranges": [], "fresh_k": None, "fresh_v": None})
+
+
 @pytest.mark.gpu
 def test_both_paths_agree(monkeypatch):
     torch, nat = _binding()
