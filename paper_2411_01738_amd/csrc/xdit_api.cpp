@@ -261,6 +261,37 @@ static int resolve_parts(const char* fn, const SplitArgs& sa, int32_t dtype, int
     return XDIT_OK;
 }
 
+// A launch whose grid has 2^32 threads or more runs only its first part, and
+// reports no error: kernels get whole batches of fewer.  The most threads
+// per query row are the float32 kernel's 8 key splits, 512 per 32 rows
+// (check_batch_bytes keeps one batch of those below the limit).
+constexpr int64_t kGridThreads = ((int64_t)1 << 32) - 1;
+
+static hipError_t launch_attn(const xdit::AttnParams& p, int32_t dtype) {
+    const int64_t per = ((int64_t)p.Nq + 31) / 32 * p.H * 512, most = kGridThreads / per;
+    const int64_t row = (int64_t)p.H * p.D * esize_of(dtype);
+    const int64_t fresh = (int64_t)p.len0 + p.len1;
+    auto at = [](auto* x, int64_t bytes) -> decltype(x) {
+        return x ? (decltype(x))((uintptr_t)x + (uintptr_t)bytes) : x;
+    };
+    for (int64_t b = 0; b < p.B; b += most) {
+        xdit::AttnParams s = p;
+        s.B = (int)(p.B - b < most ? p.B - b : most);
+        s.q = at(p.q, b * p.Nq * row);
+        s.k = at(p.k, b * p.Nk * row);
+        s.v = at(p.v, b * p.Nk * row);
+        s.fresh_k = at(p.fresh_k, b * fresh * row);
+        s.fresh_v = at(p.fresh_v, b * fresh * row);
+        s.wk = at(p.wk, b * p.Nk * row);
+        s.wv = at(p.wv, b * p.Nk * row);
+        s.out = at(p.out, b * p.Nq * row);
+        s.lse = at(p.lse, b * p.H * p.Nq * 4);
+        const hipError_t e = dtype == XDIT_BF16 ? xdit::launch_attn_bf16(s, g_stream) : xdit::launch_attn_f32(s, g_stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Launch a partitioned attention: the sweep workgroups, then the fix-up of
 // cut sweeps (both inside launch_attn_bf16).
 static hipError_t launch_parts(xdit::AttnParams p, const Partition& pt, void* workspace) {
@@ -313,9 +344,7 @@ static int chunk_impl(const char* fn, const void* q, const void* k, const void* 
     p.D = (int)head_dim;
     p.accum = accum;
     if (parts.parts > 0) return hip_status(launch_parts(p, parts, sa.workspace), fn);
-    const hipError_t e = dtype == XDIT_BF16 ? xdit::launch_attn_bf16(p, g_stream)
-                                            : xdit::launch_attn_f32(p, g_stream);
-    return hip_status(e, fn);
+    return hip_status(launch_attn(p, dtype), fn);
 }
 
 int xdit_chunk_attn(const void* q, const void* k, const void* v, void* out, float* lse,
@@ -457,9 +486,7 @@ static int patch_ranges_impl(const char* fn, const void* q, int64_t q_len, void*
     p.off1 = (int)off[1];
     p.len1 = (int)len[1];
     if (parts.parts > 0) return hip_status(launch_parts(p, parts, sa.workspace), fn);
-    const hipError_t e = dtype == XDIT_BF16 ? xdit::launch_attn_bf16(p, g_stream)
-                                            : xdit::launch_attn_f32(p, g_stream);
-    return hip_status(e, fn);
+    return hip_status(launch_attn(p, dtype), fn);
 }
 
 int xdit_patch_attn(const void* q, void* kv_buf, int64_t patch_off, int64_t patch_len,

@@ -9,7 +9,7 @@ import pytest
 import oracle
 import paper_2411_01738_amd as xd
 from paper_2411_01738_amd.inputs import WORKLOADS, generate, random_io
-from tests.gpu_util import check_lse, check_out, tdtype, to_gpu, to_np, torch_mod
+from tests.gpu_util import TOL, check_lse, check_out, tdtype, to_gpu, to_np, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -106,6 +106,22 @@ def test_chunk_empty_q_is_noop(torch):
     out = torch.zeros((1, 0, 2, 64), device="cuda", dtype=torch.bfloat16)
     xd.xdit_chunk_attn(q, k, k.clone(), out, None)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_chunk_of_more_workgroups_than_one_grid_holds(torch, dtype):
+    """17.6 million (batch, head) pairs of one query: more than 2^32 threads
+    in all.  With one key the output is V's row and the LSE the score."""
+    B, H, d = 1100, 16000, 64
+    r = lambda: torch.randn(B, 1, H, d, device="cuda").to(tdtype(dtype))
+    q, k, v = r(), r(), r()
+    out = torch.full_like(v, float("nan"))
+    lse = _lse_buf(torch, B, H, 1)
+    xd.xdit_chunk_attn(q, k, v, out, lse)
+    assert torch.equal(out, v)
+    ref = (q[:, 0].float() * k[:, 0].float()).sum(-1) / d ** 0.5
+    err = ((lse[:, :, 0] - ref).abs() / ref.abs().clamp(min=1)).max().item()
+    assert err <= TOL[dtype]["lse_rel"]
 
 
 @pytest.mark.parametrize("d", [64, 72, 128])
