@@ -290,6 +290,8 @@ def xdit_lse_merge(outs, lses, n: int, out, lse_out=None) -> None:
             raise XditError(-3, f"outs[{r}] does not match out")
         if tuple(lses[r].shape) != (B, H, Nq) or lses[r].dtype != torch.float32:
             raise XditError(-3, f"lses[{r}] must be float32 {(B, H, Nq)}")
+    if lse_out is not None and (tuple(lse_out.shape) != (B, H, Nq) or lse_out.dtype != torch.float32):
+        raise XditError(-3, f"lse_out must be float32 {(B, H, Nq)}")
     optrs = (ctypes.c_void_p * n)(*[outs[r].data_ptr() for r in range(n)])
     lptrs = (ctypes.c_void_p * n)(*[lses[r].data_ptr() for r in range(n)])
     _use_current_stream()

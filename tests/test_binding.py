@@ -91,6 +91,22 @@ def test_patch_forms_check_shapes_and_types(checks_only, call):
         f(**{**good, "ranges": [], "fresh_k": None, "fresh_v": None})
 
 
+def test_merge_checks_the_merged_lse(checks_only):
+    """A merged LSE that is short, of another type or of other sizes would be
+    written past its end."""
+    import torch
+
+    t, f32 = checks_only, torch.float32
+    B, Nq, H, d = 1, 6, 2, 64
+    outs, lses = [t(B, Nq, H, d)] * 2, [t(B, H, Nq, dt=f32)] * 2
+    for lse in (None, t(B, H, Nq, dt=f32)):
+        with pytest.raises(AssertionError, match="was launched"):
+            xd.xdit_lse_merge(outs, lses, 2, t(B, Nq, H, d), lse)
+    for bad in (t(B, H, Nq - 1, dt=f32), t(B, 1, Nq, dt=f32), t(B, H, Nq)):
+        with pytest.raises(XditError):
+            xd.xdit_lse_merge(outs, lses, 2, t(B, Nq, H, d), bad)
+
+
 @pytest.mark.gpu
 def test_both_paths_agree(monkeypatch):
     torch, nat = _binding()
