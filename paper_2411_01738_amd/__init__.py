@@ -77,6 +77,12 @@ def _dense(t, name: str, ndim: int):
     return t
 
 
+def _buffer(kv_buf):
+    _dense(kv_buf, "kv_buf", 5)
+    if kv_buf.shape[0] < 2:
+        raise XditError(-3, f"kv_buf must be [2, B, N, H, d] (K's plane, then V's), got {tuple(kv_buf.shape)}")
+
+
 def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
@@ -104,7 +110,7 @@ def xdit_patch_attn(q, kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v,
     nat = _native if _native is not None else _load_native()
     if nat and _done(nat.patch(q, kv_buf, patch_off, patch_len, fresh_k, fresh_v, out)):
         return
-    _dense(kv_buf, "kv_buf", 5)
+    _buffer(kv_buf)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
     _, B, N, H, d = kv_buf.shape
@@ -120,7 +126,7 @@ def xdit_patch_attn(q, kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v,
 
 
 def _patch_args(q, kv_buf, ranges, fresh_k, fresh_v, out, lse):
-    _dense(kv_buf, "kv_buf", 5)
+    _buffer(kv_buf)
     for t, n in ((q, "q"), (fresh_k, "fresh_k"), (fresh_v, "fresh_v"), (out, "out")):
         _dense(t, n, 4)
     _dense(lse, "lse", 3)
@@ -305,7 +311,7 @@ def xdit_kv_update(kv_buf, patch_off: int, patch_len: int, fresh_k, fresh_v) -> 
     nat = _native if _native is not None else _load_native()
     if nat and _done(nat.update(kv_buf, patch_off, patch_len, fresh_k, fresh_v)):
         return
-    _dense(kv_buf, "kv_buf", 5)
+    _buffer(kv_buf)
     _dense(fresh_k, "fresh_k", 4)
     _dense(fresh_v, "fresh_v", 4)
     _, B, N, H, d = kv_buf.shape
@@ -322,7 +328,7 @@ def xdit_stage_step(x, wq, wk, wv, wo, kv_buf, patch_off: int, q, k, v, o, y) ->
     W{q,k,v} (x [B,L,C], W [C,H*d]), the patch step over kv_buf [2,B,N,H,d]
     at rows [patch_off, patch_off+L) with fresh K/V (k, v) and output o, then
     y = o wo (wo [H*d,C]).  q, k, v, o [B,L,H,d] and y [B,L,C] are written."""
-    _dense(kv_buf, "kv_buf", 5)
+    _buffer(kv_buf)
     _, B, N, H, d = kv_buf.shape
     _dense(x, "x", 3)
     L, C = x.shape[1], x.shape[2]

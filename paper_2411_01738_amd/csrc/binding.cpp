@@ -34,6 +34,9 @@ bool get(PyObject* o, int64_t dims, T* t) {
     return true;
 }
 
+// a K/V buffer: K's plane, then V's
+bool buffer(PyObject* o, T* t) { return get(o, 5, t) && t->s[0] >= 2; }
+
 bool get_or_none(PyObject* o, int64_t dims, T* t) { return o == Py_None || get(o, dims, t); }
 
 bool shape4(const T& t, at::ScalarType dt, int64_t a, int64_t b, int64_t c, int64_t d) {
@@ -168,7 +171,7 @@ PyObject* patch(PyObject* const* a) {
     T q, kv, fk, fv, out;
     int64_t off, len;
     int32_t dt;
-    if (!get(a[0], 4, &q) || !get(a[1], 5, &kv) || !integer(a[2], &off) || !integer(a[3], &len) || !get(a[4], 4, &fk) ||
+    if (!get(a[0], 4, &q) || !buffer(a[1], &kv) || !integer(a[2], &off) || !integer(a[3], &len) || !get(a[4], 4, &fk) ||
         !get(a[5], 4, &fv) || !get(a[6], 4, &out) || !code(kv.dt, &dt))
         Py_RETURN_NONE;
     const int64_t B = kv.s[1], N = kv.s[2], H = kv.s[3], d = kv.s[4];
@@ -183,7 +186,7 @@ PyObject* general_patch(PyObject* const* a) {
     T q, kv, fk, fv, out, lse, ws;
     int64_t off[XDIT_MAX_RANGES] = {}, len[XDIT_MAX_RANGES] = {}, F, splits = 0;
     int32_t dt, nr;
-    if (!get(a[0], 4, &q) || !get(a[1], 5, &kv) || !ranges(a[2], off, len, &nr, &F) || !get(a[3], 4, &fk) ||
+    if (!get(a[0], 4, &q) || !buffer(a[1], &kv) || !ranges(a[2], off, len, &nr, &F) || !get(a[3], 4, &fk) ||
         !get(a[4], 4, &fv) || !get(a[5], 4, &out) || !get_or_none(a[6], 3, &lse) || !code(kv.dt, &dt) ||
         (SPLIT && (!integer(a[7], &splits) || splits != (int32_t)splits || !get_or_none(a[8], -1, &ws))))
         Py_RETURN_NONE;
@@ -231,8 +234,8 @@ PyObject* update(PyObject* const* a) {
     T kv, fk, fv;
     int64_t off, len;
     int32_t dt;
-    if (!get(a[0], 5, &kv) || !integer(a[1], &off) || !integer(a[2], &len) || !get(a[3], 4, &fk) || !get(a[4], 4, &fv) ||
-        !code(kv.dt, &dt))
+    if (!buffer(a[0], &kv) || !integer(a[1], &off) || !integer(a[2], &len) || !get(a[3], 4, &fk) ||
+        !get(a[4], 4, &fv) || !code(kv.dt, &dt))
         Py_RETURN_NONE;
     const int64_t B = kv.s[1], N = kv.s[2], H = kv.s[3], d = kv.s[4];
     if (!shape4(fk, kv.dt, B, len, H, d) || !shape4(fv, kv.dt, B, len, H, d)) Py_RETURN_NONE;

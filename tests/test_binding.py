@@ -107,6 +107,37 @@ def test_merge_checks_the_merged_lse(checks_only):
             xd.xdit_lse_merge(outs, lses, 2, t(B, Nq, H, d), bad)
 
 
+def test_buffer_has_both_planes(checks_only):
+    """V's plane starts where K's ends: a buffer of one plane has none."""
+    t = checks_only
+    B, N, H, d, n = 1, 8, 2, 64, 4
+    x = t(B, n, H, d)
+    calls = [lambda kv: xd.xdit_patch_attn(x, kv, 0, n, x, x, x), lambda kv: xd.xdit_kv_update(kv, 0, n, x, x),
+             lambda kv: xd.xdit_patch_attn_ranges(x, kv, [(0, n)], x, x, x),
+             lambda kv: xd.xdit_patch_attn_split(x, kv, [(0, n)], x, x, x),
+             lambda kv: xd.xdit_stage_step(t(B, n, 64), *[t(64, H * d)] * 3, t(H * d, 64), kv, 0, x, x, x, x, t(B, n, 64))]
+    for call in calls:
+        with pytest.raises(AssertionError, match="was launched"):
+            call(t(2, B, N, H, d))
+        with pytest.raises(XditError):
+            call(t(1, B, N, H, d))
+
+
+@pytest.mark.gpu
+def test_native_path_declines_a_buffer_of_one_plane():
+    torch, nat = _binding()
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    B, N, H, d, n = 1, 8, 2, 64, 4
+    z = lambda *s: torch.zeros(*s, device="cuda", dtype=torch.bfloat16)
+    x, o = z(B, n, H, d), z(B, n, H, d)
+    kv = z(2, B, N, H, d)[:1]  # the library would find the second plane's memory
+    assert nat.patch(x, kv, 0, n, x, x, o) is None
+    assert nat.patch_ranges(x, kv, [(0, n)], x, x, o, None) is None
+    assert nat.patch_split(x, kv, [(0, n)], x, x, o, None, 1, None) is None
+    assert nat.update(kv, 0, n, x, x) is None
+
+
 @pytest.mark.gpu
 def test_both_paths_agree(monkeypatch):
     torch, nat = _binding()
