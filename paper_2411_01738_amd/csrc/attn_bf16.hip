@@ -1340,6 +1340,25 @@ static int attn_kernel_choice() {
     return 0;
 }
 
+// d = 128, no more workgroups than CUs: whether a quad is ahead of the 8 waves
+// of wide, which have twice the waves per row but a merge and 64-key tiles.
+// `keys`: of one workgroup's sweep.  Measured, us for quad / wide:
+//   * short sweeps, where the merge costs more than the waves give (24 heads,
+//     1000 queries; 1, 96, 160 and 256 keys): 6.9 / 7.8, 7.9 / 8.8, 8.9 / 9.5,
+//     10.6 / 10.1; split calls likewise (24 heads of 100 queries in 2 parts of
+//     96, 160 and 384 keys: 11.7 / 12.9, 12.6 / 13.4, 16.1 / 15.8).  The line is the two times'
+//     growth per tile.
+//   * one query tile per head on nearly all CUs: nothing shares its K/V, and
+//     the reads bound it (split calls of 24 heads of 64 queries: 8448 keys in
+//     240 parts 29.4 / 30.8; 48 heads 42.3 / 46.2, of 128 queries 44-46 / 46-47;
+//     with 192 parts 22.9 / 23.2; unsplit 200 heads of 65, 384 and
+//     1024 keys: 12.0 / 12.9, 22.8 / 21.4; 256 heads of 65, 1024 keys: 24.8 /
+//     26.9).
+static bool quad_ahead(int64_t workgroups, int64_t Nq, int64_t keys) {
+    const int64_t q = (keys + 31) / 32, w = (keys + 63) / 64;
+    return 0.53 * q < 0.82 * w + 0.6 || (Nq <= 128 && (workgroups > 224 || (workgroups > 192 && keys <= 512)));
+}
+
 // The shape of an unpartitioned launch.
 //   * No more 128-row query tiles than CUs: the 8-wave shapes.  Two waves of
 //     a SIMD then work on the same rows, where a 4-wave workgroup would be
@@ -1351,7 +1370,11 @@ static int attn_kernel_choice() {
 //     shortest chain of a wave wins (d = 64, 24 heads, 300 x 4429: strip 24.5
 //     us, narrow 27.5; 16 x 2500: 15.1 and 17.0; d = 72, 2 x 16 heads, 256 x
 //     4096: 29.2 and 30.0; d = 128, 24 heads, 200 x 4224: strip 46.8, wide
-//     58.5; 100 x 500, 12 heads: 10.0 and 12.4).
+//     58.5; 100 x 500, 12 heads: 10.0 and 12.4), but for short sweeps at d =
+//     128, where a quad's time grows by 0.52 us per 32 keys and by 0.015 us
+//     per row of a tile, strip's by 0.52 us per 64 keys (24 heads, quad and
+//     strip: 17 x 1 4.4 and 5.5 us, 17 x 160 6.2 and 6.5, 33 x 96 5.4 and 6.0,
+//     33 x 128 5.9 both, 64 x 96 6.0 and 6.2, 100 x 64 6.1 and 5.6).
 //   * More: the cheapest by a model of the rounds, in units of a 128-key
 //     tile swept by a full round of quads (two per CU):
 //       quad: 1 per tile and full round, 0.58 when at most half of the
@@ -1373,9 +1396,12 @@ static int attn_kernel_choice() {
 Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
     const int64_t n = (Nq + 127) / 128 * bh;
     const int64_t strip_rows = D > 96 ? 64 : 32;
-    if ((Nq + strip_rows - 1) / strip_rows * bh <= kCUs) return kStrip;
+    if ((Nq + strip_rows - 1) / strip_rows * bh <= kCUs) {
+        const int64_t q = (Nk + 31) / 32, w = (Nk + 63) / 64, r = Nq < 128 ? Nq : 128;
+        return D > 96 && 0.52 * (q - w) + 0.015 * r < 1.5 ? kQuad : kStrip;
+    }
     if (n <= kCUs) {
-        if (D > 96) return kWide;
+        if (D > 96) return quad_ahead(n, Nq, Nk) ? kQuad : kWide;
         const int64_t narrow = (Nq + 63) / 64 * bh;
         const double qfill_w = (double)Nq / ((Nq + 127) / 128 * 128.0);
         const double qfill_n = (double)Nq / ((Nq + 63) / 64 * 64.0);
@@ -1406,9 +1432,18 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
     if (p.parts > 0) {
         // split keys fill the GPU by themselves: 128-row query tiles (the
         // slots' rows); at d = 128 quads, two per CU, unless the launch has
-        // no more workgroups than CUs
-        if constexpr (D > 96)
-            if (choice == 0 && p.whole + p.parts > kCUs) return launch<D, 4, 1, 32, PATCH>(p, s);
+        // no more workgroups than CUs (24 heads, 512 x 4224 in 192 parts: quad
+        // 50.7 us, wide 44.5; 12 heads, 1152 x 9191 in 216: 96 and 81)
+        if constexpr (D > 96) {
+            const int64_t pairs = (int64_t)((p.Nq + 127) / 128) * p.H * p.B, wgs = p.whole + p.parts;
+            const int64_t keys = p.whole > 0 ? p.Nk : (int64_t)p.Nk * pairs / p.parts;  // of the longest sweep
+            // more parts than 64-key tiles: wide leaves parts empty, which
+            // the fix-up then skips (quad and wide: 15 heads, 128 x 528 in 16
+            // parts 21.1 and 17.5 us; 24 heads, 100 x 330 in 10 18.0 and 15.9)
+            const bool spare = p.parts > pairs * ((p.Nk + 63) / 64);
+            if (choice == 0 && (wgs > kCUs || (!spare && quad_ahead(wgs, p.Nq, keys))))
+                return launch<D, 4, 1, 32, PATCH>(p, s);
+        }
         return launch<D, 4, 2, KW, PATCH>(p, s);
     }
     Shape shape = forced_shape();

@@ -66,3 +66,29 @@ def check_lse(gpu, ref, dtype: str, what: str):
     g, r = gpu[~inf_ref], ref[~inf_ref]
     rel = np.abs(g - r) / np.maximum(np.abs(r), 1.0)
     assert rel.max() <= TOL[dtype]["lse_rel"], f"{what}: LSE rel err {rel.max():.3e}"
+
+
+def attention_kernels(f) -> list[str]:
+    """Runs f; the attention kernels it launched, as "name<arguments>"."""
+    import re
+
+    from torch.profiler import ProfilerActivity, profile
+
+    torch = torch_mod()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        f()
+        torch.cuda.synchronize()
+    return [m[0] for e in p.events() if (m := re.search(r"attn_\w+<[^>]*>", e.name))]
+
+
+# template arguments <d, query blocks, key splits, keys> of the bf16 workgroup
+# shapes at head dims up to 72, and at 128
+BF16_SHAPES = {"wide": ((4, 2, 64), (4, 2, 32)), "narrow": ((2, 4, 32), None), "quad": ((4, 1, 64), (4, 1, 32)),
+               "oct": ((8, 1, 64), (8, 1, 32)), "six": ((6, 2, 32), None), "strip": ((1, 4, 32), (2, 2, 32))}
+
+
+def bf16_kernel(shape: str, d: int, patch: bool = False, parts: bool = False) -> str:
+    args = BF16_SHAPES[shape][d > 96]
+    flags = [str(x).lower() for x in (patch, parts, False)]
+    return f"attn_bf16_kernel<{', '.join(str(x) for x in (d, *args))}, {', '.join(flags)}>"

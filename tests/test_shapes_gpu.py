@@ -10,7 +10,7 @@ import pytest
 import oracle
 import paper_2411_01738_amd as xd
 from paper_2411_01738_amd.inputs import random_io, sample_rows
-from tests.gpu_util import check_lse, check_out, to_gpu, to_np, torch_mod
+from tests.gpu_util import attention_kernels, bf16_kernel, check_lse, check_out, to_gpu, to_np, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +79,31 @@ def test_picked(d, H, nq, nk):
     torch, orc = torch_mod(), oracle.get()
     print(f"[picked] d={d} H={H} {nq} x {nk}", flush=True)
     _chunk(torch, orc, 1, H, d, nq, nk, f"d={d} H={H} {nq} x {nk}", sample_rows(nq, 97, [127, 128, 191, 192, 255, 256]))
+
+
+@pytest.mark.parametrize("H,nq,nk,splits,shape", [
+    (24, 17, 1, 1, "quad"), (24, 17, 160, 1, "quad"), (24, 17, 161, 1, "strip"), (24, 64, 96, 1, "quad"),
+    (24, 64, 97, 1, "strip"), (24, 100, 64, 1, "strip"),                                 # 64-row tiles fit the CUs
+    (24, 1000, 160, 1, "quad"), (24, 1000, 192, 1, "wide"), (24, 1000, 224, 1, "quad"), (24, 1000, 225, 1, "wide"),
+    (200, 65, 512, 1, "quad"), (200, 65, 513, 1, "wide"), (225, 65, 700, 1, "quad"),     # one tile per head
+    (24, 100, 448, 2, "quad"), (24, 100, 514, 2, "wide"), (15, 128, 528, 16, "wide"),    # split calls
+    (24, 64, 6144, 10, "quad"), (12, 64, 6144, 16, "wide")])
+def test_short_sweeps_at_128(H, nq, nk, splits, shape):
+    """Head dim 128, no more workgroups than CUs: 4-wave workgroups where the
+    8-wave ones' merge, or the reads of K/V, cost more than they gain."""
+    torch, orc, d = torch_mod(), oracle.get(), 128
+    print(f"[short] H={H} {nq} x {nk} in {splits}", flush=True)
+    q, k, v = (random_io((1, n, H, d), "bf16", 70 + n + i) for i, n in enumerate((nq, nk, nk)))
+    g = [to_gpu(x, "bf16") for x in (q, k, v)]
+    out = torch.full_like(g[0], float("nan"))
+    lse = torch.full((1, H, nq), float("nan"), device="cuda")
+    if splits > 1:
+        ws = torch.empty(xd.split_workspace_bytes(g[0], nk, splits), device="cuda", dtype=torch.uint8)
+        names = attention_kernels(lambda: xd.xdit_chunk_attn_split(*g, out, lse, splits, ws))
+    else:
+        names = attention_kernels(lambda: xd.xdit_chunk_attn(*g, out, lse))
+    assert names == [bf16_kernel(shape, d, parts=splits > 1)]
+    rows, heads = sample_rows(nq, 23, [0, nq - 1]), slice(0, 2)
+    ro, rl = orc.attention(q[:, rows, heads].copy(), k[:, :, heads].copy(), v[:, :, heads].copy())
+    check_out(to_np(out)[:, rows, heads], ro, "bf16", shape)
+    check_lse(lse.cpu().numpy()[:, heads, rows], rl, "bf16", shape + " lse")
