@@ -1359,6 +1359,23 @@ static bool quad_ahead(int64_t workgroups, int64_t Nq, int64_t keys) {
     return 0.53 * q < 0.82 * w + 0.6 || (Nq <= 128 && (workgroups > 224 || (workgroups > 192 && keys <= 512)));
 }
 
+int64_t full_rounds(int64_t bh, int64_t Nq, int64_t rows) { return ((Nq + rows - 1) / rows * bh + kCUs - 1) / kCUs; }
+
+// pick_shape's model for more 128-row query tiles than CUs; a shape that the
+// head dim does not have costs what quad does.
+struct Rounds {
+    double quad, oct, six;
+};
+Rounds rounds_cost(int D, int64_t bh, int64_t Nq, int64_t Nk) {
+    const int64_t n = (Nq + 127) / 128 * bh, rem = n % (2 * kCUs);
+    const double T = (double)Nk / 128;
+    Rounds c;
+    c.quad = (double)(n / (2 * kCUs)) * (T + 0.5) + (rem == 0 ? 0 : rem <= kCUs ? 0.58 * T : T) + 2.0;
+    c.oct = D < 72 ? c.quad : full_rounds(bh, Nq, 256) * (0.95 * T + 2.9);
+    c.six = D > 96 ? c.quad : full_rounds(bh, Nq, 192) * (0.84 * T + 2.9);
+    return c;
+}
+
 // The shape of an unpartitioned launch.
 //   * No more 128-row query tiles than CUs: the 8-wave shapes.  Two waves of
 //     a SIMD then work on the same rows, where a 4-wave workgroup would be
@@ -1407,14 +1424,9 @@ Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
         const double qfill_n = (double)Nq / ((Nq + 63) / 64 * 64.0);
         return fill(narrow) * qfill_n > 1.1 * fill(n) * qfill_w ? kNarrow : kWide;
     }
-    const double T = (double)Nk / 128;
-    const int64_t rem = n % (2 * kCUs);
-    const double quad = (double)(n / (2 * kCUs)) * (T + 0.5) + (rem == 0 ? 0 : rem <= kCUs ? 0.58 * T : T) + 2.0;
-    auto rounds = [&](int64_t rows) { return (double)(((Nq + rows - 1) / rows * bh + kCUs - 1) / kCUs); };
-    const double oct = D < 72 ? quad : rounds(256) * (0.95 * T + 2.9);
-    const double six = D > 96 ? quad : rounds(192) * (0.84 * T + 2.9);
-    if (six < quad && six <= oct) return kSix;
-    return oct < quad ? kOct : kQuad;
+    const Rounds c = rounds_cost(D, bh, Nq, Nk);
+    if (c.six < c.quad && c.six <= c.oct) return kSix;
+    return c.oct < c.quad ? kOct : kQuad;
 }
 
 template <int D, bool PATCH>
@@ -1464,6 +1476,15 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
 }
 
 }  // namespace
+
+double unsplit_cost(int D, int64_t bh, int64_t Nq, int64_t Nk, double six_sweep) {
+    if (pick_shape(D, bh, Nq, Nk) != kSix) {
+        const Rounds c = rounds_cost(D, bh, Nq, Nk);
+        return 1.9 * (c.oct < c.quad ? c.oct : c.quad);
+    }
+    const int64_t r = full_rounds(bh, Nq, 192);
+    return r * six_sweep * (D < 72 && r > 1 ? 1.05 : 1.0);
+}
 
 hipError_t launch_attn_fixup(const AttnParams& p, int q_tiles, int T, hipStream_t s) {
     switch (p.D) {

@@ -62,6 +62,13 @@ constexpr int kPartSlotRows = 128;  // query rows of a partitioned launch's tile
 constexpr int kMaxSweepParts = 17;  // most partition ranges one sweep may meet
 
 hipError_t launch_attn_bf16(const AttnParams& p, hipStream_t s);
+// Time of an unpartitioned bf16 launch of more 128-row query tiles than CUs,
+// for the partition's model (pick_parts in xdit_api.cpp) and in its units;
+// six_sweep: one round of 192-row tiles.  Quad and oct cost 1.9 times what
+// pick_shape's model says (2.1-2.2 us and 2.4 us per unit of that at d = 64
+// and 72, the partition's units 1.13 and 1.3 us); 192-row tiles at d = 64
+// take 5 % more per round when there are several.
+double unsplit_cost(int D, int64_t bh, int64_t Nq, int64_t Nk, double six_sweep);
 // The second launch of a partitioned bf16 attention (128-row query tiles,
 // sweeps of T K/V tiles): merges the partials of the cut sweeps into out
 // and lse.

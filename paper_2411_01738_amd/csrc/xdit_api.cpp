@@ -164,12 +164,19 @@ static int64_t part_ws_bytes(const Partition& pt, int64_t pairs, int64_t head_di
 // A partition is taken only when the model saves at least 10 % of these.
 // Unpartitioned launches at d <= 72 of more query tiles than CUs also run
 // 192-row tiles (pick_shape in attn_bf16.hip), one workgroup per CU and
-// round, at 1.4 t + 5 (d = 64) or 1.2 t + 6.4 (d = 72) of the same units; no
-// partition is taken where those are ahead.  Measured, us cut / uncut: d = 64,
-// 2 x 24 heads, 700 x 2000 36 / 31; 12 heads, 3300 x 5000 69 / 66; 24 heads,
-// 1738 x 6941 98 / 95; d = 72, 2 x 16 heads, 1100 x 4096 64 / 59; 8 heads,
-// 4400 x 6000 85 / 80.  Beyond the line: d = 64, 24 heads, 1500 x 14000 153 /
-// 172; 48 heads, 770 x 17776 222 / 229; d = 72, 16 heads, 2234 x 12279 157 / 159.
+// round, at 1.4 t + 5 (d = 64) or 1.2 t + 6.4 (d = 72) of the same units: no
+// partition where those are ahead and the shape that the launch would run
+// (unsplit_cost; 192-row tiles mostly where they take one round) is as well.
+// Measured, us cut / uncut.  One round of 192-row tiles: d = 64, 2 x 24 heads,
+// 839 x 3780 60.7 / 56.0; 12 heads, 3322 x 3557 54.3 / 50.0; 2 x 12 heads,
+// 1693 x 8266 113 / 109; d = 72, 2 x 8 heads, 2327 x 4027 68.8 / 59.2; 8 heads,
+// 5056 x 16468 233 / 227; beyond the line d = 64, 24 heads, 1500 x 14000 153 /
+// 172; d = 72, 16 heads, 2234 x 12279 157 / 159.  More rounds, where quad
+// would run: d = 64, 24 heads, 3060 x 1319 48.4 / 40.7; 2 x 12 heads, 5579 x
+// 3575 158 / 159; 2 x 48 heads, 1374 x 8543 345 / 369; d = 72, 8 heads, 9376 x
+// 1743 68.0 / 60.5; 8 heads, 9207 x 4336 124 / 135; 192-row tiles: d = 64, 4 x
+// 24 heads, 1307 x 12496 496 / 513; d = 72, 2 x 16 heads, 4195 x 16372 737 /
+// 709; 256-row tiles: d = 72, 16 heads, 10633 x 6726 406 / 391.
 // The model counts rounds of one workgroup per CU; at d = 128 the kernel runs
 // two 4-wave workgroups per CU, for which flux's measured alternatives (whole
 // rounds of 512 with the rest cut, 512 equal ranges) were no faster than
@@ -222,7 +229,9 @@ static Partition pick_parts(int64_t bh, int64_t q_len, int64_t kv_len, int64_t h
     }
     if (head_dim <= 72 && pairs > kCUs) {
         const double sweep = head_dim < 72 ? 1.4 * t + 5.0 : 1.2 * t + 6.4;
-        if (rounds((q_len + 191) / 192 * bh) * sweep < best) return none;
+        if (rounds((q_len + 191) / 192 * bh) * sweep < best &&
+            xdit::unsplit_cost((int)head_dim, bh, q_len, kv_len, sweep) < best)
+            return none;
     }
     return best < 0.9 * plain ? pick : none;
 }

@@ -240,6 +240,19 @@ def test_chosen_partition_of_a_few_tiles_over(B, nq, nk, H, d, parts):
 
 
 @needs_no_gpu
+@pytest.mark.parametrize("B,nq,nk,H,d,parts", [
+    (1, 3060, 1319, 24, 64, 0), (1, 2786, 6108, 48, 64, 256), (2, 1374, 8543, 48, 64, 256),  # quad would run
+    (1, 9376, 1743, 8, 72, 0), (1, 9207, 4336, 8, 72, 256), (1, 8255, 6001, 16, 72, 256),
+    (4, 1307, 12496, 24, 64, 256), (2, 4195, 16372, 16, 72, 0),                              # 192-row tiles
+    (1, 10633, 6726, 16, 72, 0)])                                                            # 256-row tiles
+def test_chosen_partition_of_several_rounds(B, nq, nk, H, d, parts):
+    """More rounds than one: the tiles over are left whole only where the
+    shape that then runs takes less time than the cut."""
+    lib = _lib.lib()
+    assert lib.xdit_split_workspace_bytes(B, nq, nk, H, d, 0, 0) == parts * 128 * (d + 1) * 4
+
+
+@needs_no_gpu
 def test_split_rejections():
     lib = _lib.lib()
     need = lib.xdit_split_workspace_bytes(1, 16, 1024, 2, 64, 0, 4)
