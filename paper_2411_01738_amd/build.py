@@ -8,8 +8,10 @@ generation disabled (-Xclang -target-feature -Xclang -packed-fp32-ops).
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -64,10 +66,22 @@ def _compile(src: str) -> str:
     return obj
 
 
+def missing_for_binding() -> str | None:
+    """What build_binding needs and this machine does not have."""
+    try:
+        from torch.utils import cpp_extension
+    except ImportError:
+        return "torch"
+    if not any(os.path.exists(os.path.join(p, "torch/csrc/autograd/python_variable.h"))
+               for p in cpp_extension.include_paths()):
+        return "torch's headers"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "Python.h"
+    return None if shutil.which("g++") else "g++"
+
+
 def build_binding() -> str:
     """Compile the torch binding's call path (host code) against libxdit.so."""
-    import sysconfig
-
     import torch
     from torch.utils import cpp_extension
 
@@ -76,8 +90,8 @@ def build_binding() -> str:
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f"-isystem{p}" for p in cpp_extension.include_paths()],
            f"-isystem{sysconfig.get_paths()['include']}", os.path.join(CSRC, "binding.cpp"), "-o", tmp,
-           f"-L{HERE}", "-l:libxdit.so", *[f"-L{p}" for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10",
-           "-Wl,-rpath,$ORIGIN"]
+           f"-L{HERE}", "-l:libxdit.so", *[f"-L{p}" for p in cpp_extension.library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stdout}{r.stderr}")
@@ -86,8 +100,10 @@ def build_binding() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source, link libxdit.so and the binding; returns the
-    library's path."""
+    """Compile every source, link libxdit.so and the torch binding; returns
+    the library's path.  Without torch, its headers or a host compiler there is
+    no binding: the library alone serves C callers, and Python calls go
+    through ctypes."""
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
@@ -98,7 +114,13 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}{r.stderr}")
     os.replace(tmp, LIBRARY)
-    build_binding()
+    missing = missing_for_binding()
+    if missing is None:
+        build_binding()
+    else:
+        if os.path.exists(BINDING):
+            os.remove(BINDING)
+        print(f"no torch binding: {missing} is missing", file=sys.stderr)
     if verbose:
         print(f"built {LIBRARY}")
     return LIBRARY
