@@ -15,6 +15,7 @@ float32.  dtypes: bfloat16 or float32 (LSE always float32).
 from __future__ import annotations
 
 import ctypes
+import warnings
 
 from ._lib import (XDIT_BF16, XDIT_F32, XDIT_MAX_PARTIALS, XDIT_MAX_RANGES, XDIT_MAX_SPLITS,
                    XditError, check, lib)
@@ -39,12 +40,16 @@ def _load_native():
     global _native
     torch = _torch()
     lib()  # says what is missing if nothing is built
+    _native = False
     try:
         from . import _binding
         _binding.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
         _native = _binding
-    except (ImportError, AttributeError):
-        _native = False
+    except AttributeError:  # a torch without GPU support: no call gets past the checks
+        pass
+    except ImportError as e:
+        warnings.warn(f"the torch binding does not load ({e}): calls go through ctypes, at several times the host "
+                      "time; build it with `python -m paper_2411_01738_amd.build`", RuntimeWarning, stacklevel=3)
     return _native
 
 

@@ -36,6 +36,26 @@ def test_declines_what_python_rejects():
         xd.xdit_chunk_attn(q, q, q, q, lse)
 
 
+@pytest.mark.parametrize("binding", ["missing", "another interpreter's"])
+def test_a_binding_that_does_not_load_is_named(monkeypatch, binding):
+    """The calls still work, through ctypes, at several times the host time."""
+    import sys
+
+    pytest.importorskip("torch")
+    if binding == "missing":
+        monkeypatch.setitem(sys.modules, "paper_2411_01738_amd._binding", None)
+        monkeypatch.delattr(xd, "_binding", raising=False)
+    else:
+        class Stale:
+            def init(self, *a):
+                raise ImportError("undefined symbol")
+        monkeypatch.setattr(xd, "_binding", Stale(), raising=False)
+    monkeypatch.setattr(xd, "_native", None)
+    with pytest.warns(RuntimeWarning, match="paper_2411_01738_amd.build"):
+        assert not xd._load_native()
+    assert xd._native is False
+
+
 class _GpuTensor:
     """A host tensor that calls itself a GPU tensor: the checks in Python take
     it, and no call may get past them to the library."""
