@@ -76,7 +76,7 @@ def attention_kernels(f) -> list[str]:
 
     torch = torch_mod()
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
         f()
         torch.cuda.synchronize()
     return [m[0] for e in p.events() if (m := re.search(r"attn_\w+<[^>]*>", e.name))]

@@ -1,6 +1,7 @@
 """float32 attention at each number of key splits the dispatch chooses (1, 2,
-4 and 8 waves per query block, by the counts of queries and keys), ragged in
-queries and keys: chunk with LSE, ring step, and a patch step whose two fresh
+4 and, at head dims 64 and 72, 8 waves per query block, by the counts of
+queries and keys), ragged in queries and keys, the kernel that ran read from a
+profile: chunk with LSE, ring step, and a patch step whose two fresh
 ranges straddle tile edges, against the fp64 oracle within the float32 bars
 of gpu_util (2^-24 relative per product and sum, over a few thousand terms)."""
 from __future__ import annotations
@@ -11,18 +12,26 @@ import pytest
 import oracle
 import paper_2411_01738_amd as xd
 from paper_2411_01738_amd.inputs import random_io
-from tests.gpu_util import check_lse, check_out, to_gpu, to_np, torch_mod
+from tests.gpu_util import attention_kernels, check_lse, check_out, to_gpu, to_np, torch_mod
 
 pytestmark = pytest.mark.gpu
 
-# (queries, keys): one tile (1 split), two (2), five with a ragged end (4; at
-# the last tile some waves have no keys), many (8)
-SHAPES = [(33, 31), (129, 50), (70, 133), (40, 1505)]
+# (queries, keys, splits of the chunk, splits of the ring's two): one tile;
+# two; three; five with a ragged end (at the last tile some waves have no
+# keys); many; so many that 8 splits are ahead, the last tile of the whole
+# sweep with keys for one wave of eight, of the ring's with five
+SHAPES = [(33, 31, 1, 1), (129, 50, 2, 1), (129, 90, 4, 2), (70, 133, 4, 4), (40, 1505, 4, 4), (40, 4885, 8, 8)]
+
+
+def _kernel(d, splits, patch=False):
+    """The name of the kernel of that many splits; 4 are the most at 128."""
+    ks = min(splits, 4 if d == 128 else 8)
+    return f"attn_f32_kernel<{d}, {max(1, 4 // ks)}, {ks}, {str(patch).lower()}>"
 
 
 @pytest.mark.parametrize("d", [64, 72, 128])
-@pytest.mark.parametrize("nq,nk", SHAPES)
-def test_f32_splits(nq, nk, d):
+@pytest.mark.parametrize("nq,nk,chunk,ring", SHAPES)
+def test_f32_splits(nq, nk, chunk, ring, d):
     torch = torch_mod()
     orc = oracle.get()
     B, H = 2, 3
@@ -31,7 +40,7 @@ def test_f32_splits(nq, nk, d):
     qg, kg, vg = (to_gpu(x, "f32") for x in (q, k, v))
     out = torch.full((B, nq, H, d), float("nan"), device="cuda")
     lse = torch.full((B, H, nq), float("nan"), device="cuda")
-    xd.xdit_chunk_attn(qg, kg, vg, out, lse)
+    assert attention_kernels(lambda: xd.xdit_chunk_attn(qg, kg, vg, out, lse)) == [_kernel(d, chunk)]
     ro, rl = orc.attention(q, k, v)
     check_out(to_np(out), ro, "f32", "chunk")
     check_lse(lse.cpu().numpy(), rl, "f32", "chunk lse")
@@ -40,7 +49,8 @@ def test_f32_splits(nq, nk, d):
     out.fill_(float("nan"))
     lse.fill_(float("-inf"))
     for a, b in ((0, cut), (cut, nk)):
-        xd.xdit_chunk_attn_accum(qg, kg[:, a:b].contiguous(), vg[:, a:b].contiguous(), out, lse)
+        ka, va = kg[:, a:b].contiguous(), vg[:, a:b].contiguous()
+        assert attention_kernels(lambda: xd.xdit_chunk_attn_accum(qg, ka, va, out, lse)) == [_kernel(d, ring)]
     check_out(to_np(out), ro, "f32", "ring")
     check_lse(lse.cpu().numpy(), rl, "f32", "ring lse")
     # patch step: ranges [1, 1 + n0) and [o1, nk), edges off the tiles'
@@ -51,7 +61,9 @@ def test_f32_splits(nq, nk, d):
     fk, fv = (random_io((B, F, H, d), "f32", 9500 + d + i) for i in range(2))
     kvg = to_gpu(kv, "f32")
     out.fill_(float("nan"))
-    xd.xdit_patch_attn_ranges(qg, kvg, ranges, to_gpu(fk, "f32"), to_gpu(fv, "f32"), out, lse)
+    fkg, fvg = to_gpu(fk, "f32"), to_gpu(fv, "f32")
+    names = attention_kernels(lambda: xd.xdit_patch_attn_ranges(qg, kvg, ranges, fkg, fvg, out, lse))
+    assert names == [_kernel(d, chunk, patch=True)]
     base = 0
     for o, n in ranges:
         kv[0][:, o:o + n], kv[1][:, o:o + n] = fk[:, base:base + n], fv[:, base:base + n]
