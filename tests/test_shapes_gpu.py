@@ -17,11 +17,13 @@ pytestmark = pytest.mark.gpu
 FORCED = [("oct", 72), ("oct", 128), ("six", 64), ("six", 72), ("strip", 64), ("strip", 72), ("strip", 128)]
 
 
-def _chunk(torch, orc, B, H, d, nq, nk, what, rows=None):
+def _chunk(torch, orc, B, H, d, nq, nk, what, rows=None, shape=None):
     q, k, v = (random_io((B, n, H, d), "bf16", 5000 + n + i) for i, n in enumerate((nq, nk, nk)))
     out = torch.full((B, nq, H, d), float("nan"), device="cuda", dtype=torch.bfloat16)
     lse = torch.full((B, H, nq), float("nan"), device="cuda", dtype=torch.float32)
-    xd.xdit_chunk_attn(to_gpu(q, "bf16"), to_gpu(k, "bf16"), to_gpu(v, "bf16"), out, lse)
+    g = [to_gpu(x, "bf16") for x in (q, k, v)]
+    names = attention_kernels(lambda: xd.xdit_chunk_attn(*g, out, lse))
+    assert shape is None or names == [bf16_kernel(shape, d)]
     rows = np.arange(nq) if rows is None else rows
     ro, rl = orc.attention(q[:, rows].copy(), k, v)
     check_out(to_np(out)[:, rows], ro, "bf16", what)
@@ -35,7 +37,7 @@ def test_chunk_edges(shape, d, monkeypatch):
     rows = {"oct": 256, "six": 192, "strip": 64 if d == 128 else 32}[shape]
     for nq, nk in [(1, 1), (rows - 1, 63), (rows, 64), (rows + 1, 65), (2 * rows + 33, 645), (40, 0), (97, 130)]:
         print(f"[shape] {shape} d={d} {nq} x {nk}", flush=True)
-        _chunk(torch, orc, 1, 2, d, nq, nk, f"{shape} d={d} {nq} x {nk}")
+        _chunk(torch, orc, 1, 2, d, nq, nk, f"{shape} d={d} {nq} x {nk}", shape=shape)
 
 
 @pytest.mark.parametrize("shape,d", FORCED)
@@ -70,15 +72,21 @@ def test_patch_and_ring(shape, d, monkeypatch):
     check_lse(lse.cpu().numpy(), rl, "bf16", f"{shape} ring lse d={d}")
 
 
-@pytest.mark.parametrize("d,H,nq,nk", [(64, 43, 769, 1300), (72, 43, 850, 1300), (72, 43, 1400, 2600), (128, 64, 510, 200), (64, 8, 1024, 700),
-                                       (64, 8, 1025, 700), (128, 64, 256, 300), (128, 65, 256, 300),
-                                       (128, 65, 510, 300), (128, 43, 1300, 2600)])
-def test_picked(d, H, nq, nk):
-    """One workgroup per CU or fewer and just above, where the library goes
-    over to 192-row and 256-row tiles."""
+@pytest.mark.parametrize("d,H,nq,nk,shape", [
+    (64, 43, 769, 1300, "six"), (72, 43, 850, 1300, "six"), (64, 8, 1024, 700, "strip"), (64, 8, 1025, 700, "narrow"),
+    (64, 43, 700, 200, "quad"), (72, 43, 1400, 2600, "quad"),
+    (72, 42, 1400, 2600, "oct"), (128, 42, 1400, 2600, "oct"),  # 252 tiles of 256 rows: one round
+    (128, 43, 1400, 2600, "quad"),                              # 258: two
+    (128, 43, 1300, 2600, "quad"), (128, 64, 510, 200, "quad"), (128, 64, 510, 300, "wide"), (128, 65, 510, 300, "quad"),
+    (128, 64, 256, 300, "strip"), (128, 65, 256, 300, "wide")])
+def test_picked(d, H, nq, nk, shape):
+    """The library's own choice: 32- or 64-row tiles up to one workgroup per
+    CU, 8 waves of 64 or 128 rows up to there, then 192-row and 256-row tiles
+    where they take fewer rounds than the 128-row ones of 4 waves."""
     torch, orc = torch_mod(), oracle.get()
     print(f"[picked] d={d} H={H} {nq} x {nk}", flush=True)
-    _chunk(torch, orc, 1, H, d, nq, nk, f"d={d} H={H} {nq} x {nk}", sample_rows(nq, 97, [127, 128, 191, 192, 255, 256]))
+    rows = sample_rows(nq, 97, [127, 128, 191, 192, 255, 256])
+    _chunk(torch, orc, 1, H, d, nq, nk, f"d={d} H={H} {nq} x {nk}", rows, shape)
 
 
 @pytest.mark.parametrize("H,nq,nk,splits,shape", [
