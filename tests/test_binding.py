@@ -1,6 +1,7 @@
 """The native call path takes only what the checks in Python would pass: a
 call it does not take comes back as None, so that the Python path raises what
-it always raised; on the GPU, calls by both paths give the same bytes."""
+it always raised; on the GPU it takes the calls it should, and they give the
+same bytes by both paths."""
 from __future__ import annotations
 
 import pytest
@@ -16,12 +17,25 @@ def _binding():
     return torch, nat
 
 
-def test_declines_what_python_rejects():
+class _Recorder:
+    """The native module, with the names and results of its calls."""
+
+    def __init__(self, nat):
+        self.nat, self.results = nat, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            rc = getattr(self.nat, name)(*args)
+            self.results.append((name, rc))
+            return rc
+        return call
+
+
+def test_declines_host_tensors():
     torch, nat = _binding()
     q = torch.zeros(1, 4, 2, 64)
     kv = torch.zeros(2, 1, 8, 2, 64)
     lse = torch.zeros(1, 2, 4)
-    # host tensors, wrong types of arguments, missing LSE
     assert nat.chunk(q, q, q, q, lse, False) is None
     assert nat.chunk(None, q, q, q, None, False) is None
     assert nat.chunk_split(q, q, q, q, lse, "2", None, False) is None
@@ -197,7 +211,11 @@ def test_both_paths_agree(monkeypatch):
         torch.cuda.synchronize()
         return out + [kv]
 
+    rec = _Recorder(nat)
+    monkeypatch.setattr(xd, "_native", rec)
     fast = calls()
+    assert rec.results == [(name, 0) for name in ("chunk", "chunk", "chunk_split", "chunk_split", "patch", "patch_ranges",
+                                                  "patch_split", "merge", "update", "chunk")]
     monkeypatch.setattr(xd, "_native", False)
     for a, b in zip(fast, calls()):
         assert torch.equal(a, b)
@@ -210,23 +228,70 @@ def test_rejections_are_the_same(monkeypatch):
         pytest.skip("no GPU visible")
     z = lambda *s, dt=torch.bfloat16: torch.zeros(*s, device="cuda", dtype=dt)
     q, kv, lse = z(1, 4, 2, 64), z(2, 1, 8, 2, 64), z(1, 2, 4, dt=torch.float32)
-    bad = [lambda: xd.xdit_chunk_attn(q, q, z(1, 5, 2, 64), z(1, 4, 2, 64)),
-           lambda: xd.xdit_chunk_attn(q, q, q, q),                                    # out aliases q
-           lambda: xd.xdit_chunk_attn(q.half(), q, q, q),
-           lambda: xd.xdit_chunk_attn(q, q.transpose(1, 2), q, z(1, 4, 2, 64)),
-           lambda: xd.xdit_chunk_attn(q, q, q, z(1, 4, 2, 64), lse[:, :, :3]),
-           lambda: xd.xdit_chunk_attn_accum(q, q, q, z(1, 4, 2, 64), None),
-           lambda: xd.xdit_patch_attn(q, kv, 6, 4, q, q, z(1, 4, 2, 64)),             # past the buffer
-           lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 2), (1, 2)], q, q, z(1, 4, 2, 64)),
-           lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 1), (2, 1), (4, 2)], q, q, z(1, 4, 2, 64)),
-           lambda: xd.xdit_lse_merge([q], [lse], 2, z(1, 4, 2, 64)),
-           lambda: xd.xdit_kv_update(kv, -1, 4, q, q),
-           lambda: xd.xdit_chunk_attn_split(q, kv[0], kv[1], z(1, 4, 2, 64), None, 17)]
+    # the library's status where the native path passes the call on, None
+    # where it leaves the refusal to the checks in Python
+    bad = [(None, lambda: xd.xdit_chunk_attn(q, q, z(1, 5, 2, 64), z(1, 4, 2, 64))),
+           (-6, lambda: xd.xdit_chunk_attn(q, q, q, q)),                                    # out aliases q
+           (None, lambda: xd.xdit_chunk_attn(q.half(), q, q, q)),
+           (None, lambda: xd.xdit_chunk_attn(q, q.transpose(1, 2), q, z(1, 4, 2, 64))),
+           (None, lambda: xd.xdit_chunk_attn(q, q, q, z(1, 4, 2, 64), lse[:, :, :3])),
+           (None, lambda: xd.xdit_chunk_attn_accum(q, q, q, z(1, 4, 2, 64), None)),
+           (-4, lambda: xd.xdit_patch_attn(q, kv, 6, 4, q, q, z(1, 4, 2, 64))),             # past the buffer
+           (-4, lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 2), (1, 2)], q, q, z(1, 4, 2, 64))),
+           (None, lambda: xd.xdit_patch_attn_ranges(q, kv, [(0, 1), (2, 1), (4, 2)], q, q, z(1, 4, 2, 64))),
+           (-4, lambda: xd.xdit_patch_attn_split(q, kv, [(0, 2), (1, 2)], q, q, z(1, 4, 2, 64))),
+           (None, lambda: xd.xdit_patch_attn_split(q, kv, [(0, 2)], q, q, z(1, 4, 2, 64))),
+           (None, lambda: xd.xdit_patch_attn_split(q, kv, [(0, 4)], q, q, z(1, 3, 2, 64))),
+           (None, lambda: xd.xdit_lse_merge([q], [lse], 2, z(1, 4, 2, 64))),
+           (None, lambda: xd.xdit_lse_merge([q], [lse], 1, z(1, 4, 2, 64), z(1, 2, 3, dt=torch.float32))),
+           (-4, lambda: xd.xdit_kv_update(kv, -1, 4, q, q)),
+           (-4, lambda: xd.xdit_chunk_attn_split(q, kv[0], kv[1], z(1, 4, 2, 64), None, 17))]
     codes = []
-    for native in (nat, False):
+    rec = _Recorder(nat)
+    for native in (rec, False):
         monkeypatch.setattr(xd, "_native", native)
-        for f in bad:
+        for _, f in bad:
             with pytest.raises(XditError) as e:
                 f()
             codes.append((e.value.code, str(e.value)))
     assert codes[:len(bad)] == codes[len(bad):]
+    assert [rc for _, rc in rec.results] == [rc for rc, _ in bad]
+
+
+@pytest.mark.gpu
+def test_declines_one_bad_argument():
+    """Arguments that would be taken but for one of another type, shape,
+    layout or device.  No call here gets as far as the library."""
+    torch, nat = _binding()
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    B, N, H, d, n = 1, 8, 2, 64, 4
+    z = lambda *s, dt=torch.bfloat16: torch.zeros(*s, device="cuda", dtype=dt)
+    f32 = torch.float32
+    x, o, kv, ws = z(B, n, H, d), z(B, n, H, d), z(2, B, N, H, d), z(256, dt=torch.uint8)
+    lse = z(B, H, n, dt=f32)
+    tensors = [x.cpu(), x.float(), x[:, :3], z(B, n, 1, d), z(B, H, n, d).transpose(1, 2), x[0], None, "x"]
+    lses = [lse.cpu(), lse.half(), lse[:, :, :3], z(B, n, H, dt=f32), "lse"]
+    forms = {  # entry: (arguments, {position: bad values})
+        "chunk": ([x, x, x, o, lse, False], {0: tensors, 2: tensors, 3: tensors, 4: lses}),
+        "chunk_split": ([x, x, x, o, lse, 2, ws, False], {1: tensors[4:] + tensors[:2], 4: lses, 5: ["2", None, 2.0, 1 << 40],
+                                                          6: [ws.cpu(), "ws"]}),
+        "patch": ([x, kv, 0, n, x, x, o], {0: tensors, 1: [kv[:1], kv[0], kv.float(), None], 2: [None, 0.0], 3: [3, 4.0],
+                                           5: tensors, 6: tensors}),
+        "patch_ranges": ([x, kv, [(0, 1), (3, 3)], x, x, o, lse],
+                         {0: tensors, 1: [kv[:1]], 2: [None, [(0, 1)], [(0, 1), [3, 3]], [(0, 1.0), (3, 3)], [(0, 1)] * 3,
+                                                       [(0, 1, 2), (3, 3)]], 3: tensors, 4: tensors, 5: tensors, 6: lses}),
+        "patch_split": ([x, kv, ((0, 4),), x, x, o, lse, 2, ws], {0: tensors, 1: [kv[:1]], 2: [((0, 3),)], 3: tensors,
+                                                                  5: tensors, 6: lses, 7: ["2", None], 8: [ws.cpu()]}),
+        "merge": ([[x], [lse], 1, o, lse], {0: [[t] for t in tensors] + [[], (x,)], 1: [[t] for t in lses] + [[None]],
+                                            2: [0, 2, 65, None], 3: tensors, 4: lses}),
+        "update": ([kv, 0, n, x, x], {0: [kv[:1], kv.float()], 1: [None], 2: [3], 3: tensors, 4: tensors}),
+    }
+    for name, (args, bad) in forms.items():
+        for i, values in bad.items():
+            for v in values:
+                what = tuple(v.shape) if isinstance(v, torch.Tensor) else v
+                assert getattr(nat, name)(*args[:i], v, *args[i + 1:]) is None, f"{name} took argument {i} = {what}"
+    # an LSE is needed to merge into
+    assert nat.chunk(x, x, x, o, None, True) is None
+    assert nat.chunk_split(x, x, x, o, None, 2, ws, True) is None
