@@ -26,10 +26,10 @@ def torch():
 
 @pytest.fixture(params=["auto", "wide", "narrow", "quad"])
 def tile_shape(request, monkeypatch):
-    """Workgroup shape of the bf16 kernel at head dim <= 72: 128 query rows x
-    2 key splits ("wide"), 64 x 4 ("narrow"), 4 waves of 128 rows over 64-key
-    tiles ("quad"), or the library's own choice.  d = 128 runs its own shape
-    in all four."""
+    """Workgroup shape of unsplit launches of the bf16 kernel: 128 query rows x
+    2 key splits ("wide"), 64 x 4 ("narrow", head dims up to 72), 4 waves of
+    128 rows ("quad"), or the library's own choice, which is also what
+    "narrow" gives at d = 128."""
     if request.param == "auto":
         monkeypatch.delenv("XDIT_ATTN_TILE", raising=False)
     else:
