@@ -36,9 +36,9 @@
  *   tolerance, only the work decomposition changes): XDIT_ATTN_KERNEL = o2 |
  *   w32 | pp | w64 selects the bf16 attention decomposition, XDIT_ATTN_TILE =
  *   wide | narrow | quad | oct | six | strip the workgroup shape of unsplit
- *   launches (narrow, six: head_dim <= 72; oct: 72, 128), and XDIT_PARTITION = none | balanced
- *   the partition of *_split calls made with splits <= 0.  Unset, the library
- *   chooses.
+ *   launches (narrow, six: head_dim <= 72; oct: 72, 128), and
+ *   XDIT_PARTITION = none | balanced the partition of *_split calls made with
+ *   splits <= 0.  Unset, the library chooses.
  */
 #ifndef XDIT_H
 #define XDIT_H

@@ -35,7 +35,9 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 EXTRA = {"attn_bf16.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]}
 
 
-ATTN_SOURCES = ("attn_bf16.hip", "attn_w64.hip", "attn_common.h")
+# what decides an attention launch and its time: the kernels, and the choice
+# of the partition
+ATTN_SOURCES = ("attn_bf16.hip", "attn_w64.hip", "attn_f32.hip", "attn_common.h", "xdit_api.cpp")
 
 
 def kernel_fingerprint(srcs=ATTN_SOURCES) -> str:

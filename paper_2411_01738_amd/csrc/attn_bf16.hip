@@ -1028,12 +1028,13 @@ __device__ __forceinline__ void attn_segment(const Args& a, unsigned char* lds, 
 // are remapped per group (whole sweeps, cut ranges) so that neighbouring
 // pairs share an XCD; G1 is a multiple of 8, so both groups start on XCD 0.
 // Workgroups of 4 waves (one per SIMD; but for strip, which has the CU to
-// itself) are built to run two per CU: each
-// wave is then held to 256 registers, so that every SIMD interleaves two
-// waves of independent workgroups, which no barrier keeps in step.  The 12
+// itself) are built to run two per CU: each wave is then held to 256
+// registers, so that every SIMD interleaves two waves of independent
+// workgroups, which no barrier keeps in step.  The 12
 // waves of "six" are three per SIMD, held to 168 registers.
 template <int D, int QB, int KS, int KW, bool PATCH, bool PARTS, bool PING>
-__global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && (KS == 1 || (QB == 2 && D <= 72)) ? 2 : QB * KS == 12 ? 3 : 1)) void attn_bf16_kernel(Args a) {
+__global__ __launch_bounds__(64 * QB * KS, (Cfg<D, QB, KS, KW>::TWO_PER_CU ? 2 : QB * KS == 12 ? 3 : 1))
+void attn_bf16_kernel(Args a) {
     using C = Cfg<D, QB, KS, KW>;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS_BYTES];
     if constexpr (!PARTS) {
@@ -1376,22 +1377,24 @@ Rounds rounds_cost(int D, int64_t bh, int64_t Nq, int64_t Nk) {
     return c;
 }
 
-// The shape of an unpartitioned launch.
+// The shape of an unpartitioned launch.  Figures: back-to-back launches of
+// chunk attention.
 //   * No more 128-row query tiles than CUs: the 8-wave shapes.  Two waves of
 //     a SIMD then work on the same rows, where a 4-wave workgroup would be
 //     alone on its CU with one (d = 64, 2 x 24 heads, 512 x 4429: wide 42 us,
-//     quad 46; d = 128, 24 heads, 1024 x 4224: wide 68, quad 88; 512 x 4224:
-//     58 and 75).  At d <= 72 narrow where 128-row tiles would leave many
-//     CUs idle.  Where even the smallest tiles (strip) are no more than the
-//     CUs: strip, since a CU then has a tile's latency to wait for and the
-//     shortest chain of a wave wins (d = 64, 24 heads, 300 x 4429: strip 24.5
-//     us, narrow 27.5; 16 x 2500: 15.1 and 17.0; d = 72, 2 x 16 heads, 256 x
-//     4096: 29.2 and 30.0; d = 128, 24 heads, 200 x 4224: strip 46.8, wide
-//     58.5; 100 x 500, 12 heads: 10.0 and 12.4), but for short sweeps at d =
-//     128, where a quad's time grows by 0.52 us per 32 keys and by 0.015 us
-//     per row of a tile, strip's by 0.52 us per 64 keys (24 heads, quad and
-//     strip: 17 x 1 4.4 and 5.5 us, 17 x 160 6.2 and 6.5, 33 x 96 5.4 and 6.0,
-//     33 x 128 5.9 both, 64 x 96 6.0 and 6.2, 100 x 64 6.1 and 5.6).
+//     quad 46; d = 128, 24 heads, 1024 x 4224: wide 63, quad 77; 512 x 4224:
+//     60 and 76), but for what quad_ahead says.  At d <= 72 narrow where
+//     128-row tiles would leave many CUs idle.  Where even the smallest tiles
+//     (strip) are no more than the CUs: strip, since a CU then has a tile's
+//     latency to wait for and the shortest chain of a wave wins (d = 64, 24
+//     heads, 300 x 4429: strip 24.5 us, narrow 27.3; 16 x 2500: 15.3 and 17.3;
+//     d = 72, 2 x 16 heads, 256 x 4096: 29.1 and 30.2; d = 128, 24 heads, 200 x
+//     4224: strip 48.0, wide 59.1; 100 x 500, 12 heads: 10.3 and 12.8), but
+//     for short sweeps at d = 128, where a quad's time grows by 0.52 us per 32
+//     keys and by 0.015 us per row of a tile, strip's by 0.52 us per 64 keys
+//     (24 heads, quad and strip: 17 x 1 4.4 and 5.5 us, 17 x 160 6.2 and 6.5,
+//     33 x 96 5.4 and 6.0, 33 x 128 5.9 both, 64 x 96 6.0 and 6.2, 100 x 64 6.1
+//     and 5.6).
 //   * More: the cheapest by a model of the rounds, in units of a 128-key
 //     tile swept by a full round of quads (two per CU):
 //       quad: 1 per tile and full round, 0.58 when at most half of the
@@ -1399,17 +1402,17 @@ Rounds rounds_cost(int D, int64_t bh, int64_t Nq, int64_t Nk) {
 //         epilogue mostly run under the other one's sweep;
 //       oct (d >= 72): 0.95 per tile and round of 256, plus 2.9: every K
 //         and V tile is read once for 256 rows instead of 128, but nothing
-//         covers the prologue (d = 128, 24 heads, 2048 x 8192: 208 us, quad
-//         225; 16 heads, 4096 x 4224: 131 and 136; d = 72, 16 heads, 4096 x
-//         4096: 87 and 93).  At d = 64 it is no faster (48 heads, patch of
+//         covers the prologue (d = 128, 24 heads, 2048 x 8192: 204 us, quad
+//         221; 16 heads, 4096 x 4224: 129 and 134; d = 72, 16 heads, 4096 x
+//         4096: 85 and 88).  At d = 64 it is no faster (48 heads, patch of
 //         1097 in 17776 rows: 311 us, quad 309; chunk 17776 x 2222: 584 and
 //         552);
 //       six (d <= 72): 0.84 per tile and round of 256, plus 2.9: between
 //         256 and 384 tiles of 128 rows, quads are two on some CUs and one on
 //         others, while 192-row tiles are one each (d = 64, 2 x 24 heads,
-//         845 x 4429: 67 us, quad 77-81, wide 86; d = 72, 2 x 16 heads,
-//         1500 x 4096: 69, 83 and 90; short sweeps tie: 845 x 500 14.3 and
-//         14.0, 845 x 256 10.4 and 9.3).
+//         845 x 4429: 63 us, quad 74, wide 82; d = 72, 2 x 16 heads, 1500 x
+//         4096: 67, 79 and 87; the line: 845 x 500 14.0 and 13.8, 845 x 256
+//         10.5 and 8.9).
 Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
     const int64_t n = (Nq + 127) / 128 * bh;
     const int64_t strip_rows = D > 96 ? 64 : 32;

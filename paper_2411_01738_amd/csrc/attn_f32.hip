@@ -5,9 +5,9 @@
 // (157 TFLOP/s; v_mfma_f32_32x32x2_f32 takes 64 clocks).  A 32 x 32 tile of
 // scores costs 2 * d/2 products (4096 clocks at d = 64) against about 500
 // clocks of softmax, most of which issues between the products.  B = 2, 16
-// heads of 72, 1024 queries over 1024 keys takes 93 us (104 TFLOP/s, of 154
+// heads of 72, 1024 queries over 1024 keys takes 94 us (102 TFLOP/s, of 154
 // that a large float32 matrix product reaches); the matrix cores are busy for
-// 66 us of them.  One query per lane with vector FMAs, as this kernel did
+// 67 us of them.  One query per lane with vector FMAs, as this kernel did
 // before, took 789 us.
 //
 // Work decomposition: one workgroup = QB blocks of 32 query rows x KS waves
@@ -208,8 +208,9 @@ __global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && KS * D > 320 ? 1 : 2
     };
     // V operands of this wave's 32 keys: k-step i is key 8(i/4) + 4hf + i%4
     // (the order of the weights), vv[i][db] dim DBLK c + db, so that one load
-    // brings a lane its dims of all blocks; the tail's k-step p holds dims 64 + lane%16 of the keys its regrouped weights hold, row
-    // 8(p/2) + 2(p%2) + trow.
+    // brings a lane its dims of all blocks; the tail's k-step p holds dims
+    // 64 + lane%16 of the keys its regrouped weights hold, row 8(p/2) +
+    // 2(p%2) + trow.
     const int grp = lane >> 4, l16 = lane & 15;
     auto vkey = [&](int i) { return kh * kKT + 8 * (i >> 2) + 4 * hf + (i & 3); };
     const int trow = (grp & 1) + 4 * (grp >> 1);
@@ -294,12 +295,12 @@ __global__ __launch_bounds__(64 * QB * KS, (QB * KS == 4 && KS * D > 320 ? 1 : 2
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // Scores of tile t into sn (QK; raw, before the scale), with the softmax of the previous tile's
-    // scores sc between the products (SM), and with(n) after product n: a product holds the matrix pipe
-    // for 64 clocks, under which a dozen VALU instructions of the same wave
-    // issue.  Left to itself each phase of the two waves of a SIMD met the
-    // same phase of the other (they share the pipe evenly, so they reach the
-    // softmax together).
+    // Scores of tile t into sn (QK; raw, before the scale), with the softmax
+    // of the previous tile's scores sc between the products (SM), and with(n)
+    // after product n: a product holds the matrix pipe for 64 clocks, under
+    // which a dozen VALU instructions of the same wave issue.  Left to itself
+    // each phase of the two waves of a SIMD met the same phase of the other
+    // (they share the pipe evenly, so they reach the softmax together).
     auto phase = [&](int t, f32x16& sc, f32x16& sn, auto qk_c, auto sm_c, auto&& with) {
         constexpr bool QK = decltype(qk_c)::value, SM = decltype(sm_c)::value;
         constexpr int NS = 4 * C::KQ;
@@ -614,10 +615,12 @@ hipError_t launch(const AttnParams& p, hipStream_t s) {
 // for KS = 1, 2, 4, 8).  Four waves alone on a CU run 10 % slower per tile
 // than two such groups in turn; so do, by 20 %, the workgroups of KS = 4 at
 // d = 128, whose LDS admits one per CU.  Measured, us for KS = 1 / 2 / 4 / 8:
-//   2 x 16 heads of 72, 1024 queries, 1024 keys   111 / 102 / 104 / 119
-//   24 heads of 64, 1000 queries, 1000 keys        83 /  76 /  64 /  70
-//   24 heads of 64, 16 queries, 2500 keys         188 /  98 /  55 /  53
-//   24 heads of 128, 512 queries, 1024 keys       143 /  80 /  90
+//   2 x 16 heads of 72, 1024 queries, 1024 keys   101 / 94 / 100 / 119
+//   24 heads of 64, 1000 queries, 1000 keys        79 /  75 /  62 /  70
+//   24 heads of 64, 16 queries, 2500 keys         187 /  97 /  55 /  52
+//   2 x 3 heads of 64, 40 queries, 1505 keys      115 /  60 /  34 /  33
+//   24 heads of 128, 512 queries, 1024 keys       141 /  79 /  90
+//   12 heads of 128, 256 queries, 2000 keys       270 / 143 /  83
 template <int D, bool PATCH>
 hipError_t dispatch(const AttnParams& p, hipStream_t s) {
     const int64_t bh = (int64_t)p.B * p.H;

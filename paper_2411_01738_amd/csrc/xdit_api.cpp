@@ -177,10 +177,10 @@ static int64_t part_ws_bytes(const Partition& pt, int64_t pairs, int64_t head_di
 // 1743 68.0 / 60.5; 8 heads, 9207 x 4336 124 / 135; 192-row tiles: d = 64, 4 x
 // 24 heads, 1307 x 12496 496 / 513; d = 72, 2 x 16 heads, 4195 x 16372 737 /
 // 709; 256-row tiles: d = 72, 16 heads, 10633 x 6726 406 / 391.
-// The model counts rounds of one workgroup per CU; at d = 128 the kernel runs
-// two 4-wave workgroups per CU, for which flux's measured alternatives (whole
-// rounds of 512 with the rest cut, 512 equal ranges) were no faster than
-// this choice.
+// The model counts rounds of one workgroup per CU; at d = 128 launches of more
+// than 256 run two 4-wave workgroups per CU, for which flux's measured
+// alternatives (whole rounds of 512 with the rest cut, 512 equal ranges) were
+// no faster than this choice.
 // XDIT_PARTITION=balanced instead cuts the whole launch into 256 equal
 // ranges (ranges cross query tiles; it loses the K/V reuse, so it is never
 // chosen; tests use it), XDIT_PARTITION=none forces no partition.
@@ -295,7 +295,8 @@ static hipError_t launch_attn(const xdit::AttnParams& p, int32_t dtype) {
         s.wv = at(p.wv, b * p.Nk * row);
         s.out = at(p.out, b * p.Nq * row);
         s.lse = at(p.lse, b * p.H * p.Nq * 4);
-        const hipError_t e = dtype == XDIT_BF16 ? xdit::launch_attn_bf16(s, g_stream) : xdit::launch_attn_f32(s, g_stream);
+        const hipError_t e =
+            dtype == XDIT_BF16 ? xdit::launch_attn_bf16(s, g_stream) : xdit::launch_attn_f32(s, g_stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
