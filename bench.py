@@ -47,16 +47,16 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E (published)
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch, one counter per run), scaled by
 # what the same counters read for kv_update_kernel copying a known size
 # (FETCH x about 1.995, WRITE x 1.0).  Each entry holds the fingerprint of the
-# kernel build it was taken on (sha256 prefix of the source and its compile
+# kernel build it was taken on (sha256 prefix of the sources and their compile
 # flags); a different build reports null.
 MEASURED_TRAFFIC = {
-    ("pixart", "patch_attn"): {"bytes": (49388 + 13876) * 1024, "src": "a32e480031cb7edd"},
-    ("sd3", "patch_attn"): {"bytes": (59086 + 9216) * 1024, "src": "a32e480031cb7edd"},
+    ("pixart", "patch_attn"): {"bytes": (49250 + 13878) * 1024, "src": "e20cf9437eea5105"},
+    ("sd3", "patch_attn"): {"bytes": (59113 + 9216) * 1024, "src": "e20cf9437eea5105"},
     # the partitioned sweep and its fix-up, one launch of each per call
-    ("flux", "chunk_attn"): {"bytes": (139891 + 41225) * 1024, "src": "a32e480031cb7edd"},
-    ("flux_ring", "chunk_attn"): {"bytes": (158658 + 41277) * 1024, "src": "a32e480031cb7edd"},
-    ("cog", "patch_attn"): {"bytes": (259249 + 19744) * 1024, "src": "a32e480031cb7edd"},
-    ("cog", "chunk_attn"): {"bytes": (133430 + 109990) * 1024, "src": "a32e480031cb7edd"},
+    ("flux", "chunk_attn"): {"bytes": (139889 + 41225) * 1024, "src": "e20cf9437eea5105"},
+    ("flux_ring", "chunk_attn"): {"bytes": (158721 + 41263) * 1024, "src": "e20cf9437eea5105"},
+    ("cog", "patch_attn"): {"bytes": (259244 + 19744) * 1024, "src": "e20cf9437eea5105"},
+    ("cog", "chunk_attn"): {"bytes": (133480 + 109990) * 1024, "src": "e20cf9437eea5105"},
 }
 
 
@@ -84,16 +84,16 @@ def traffic_of(workload: str, kind: str) -> dict:
 # summary file and the kernel build's fingerprint; a different build reports
 # nothing.
 MEASURED_COUNTERS = {
-    ("pixart", "patch_attn"): {"mfma_busy": 0.379, "file": "profiles/attn_patch_pixart_mfma_counters.txt",
-                               "src": "a32e480031cb7edd"},
+    ("pixart", "patch_attn"): {"mfma_busy": 0.378, "file": "profiles/attn_patch_pixart_mfma_counters.txt",
+                               "src": "e20cf9437eea5105"},
     ("sd3", "patch_attn"): {"mfma_busy": 0.353, "file": "profiles/attn_patch_sd3_mfma_counters.txt",
-                            "src": "a32e480031cb7edd"},
+                            "src": "e20cf9437eea5105"},
     ("flux", "chunk_attn"): {"mfma_busy": 0.531, "file": "profiles/attn_chunk_flux_mfma_counters.txt",
-                             "src": "a32e480031cb7edd"},
+                             "src": "e20cf9437eea5105"},
     ("cog", "patch_attn"): {"mfma_busy": 0.406, "file": "profiles/attn_patch_cog_mfma_counters.txt",
-                            "src": "a32e480031cb7edd"},
+                            "src": "e20cf9437eea5105"},
     ("cog", "chunk_attn"): {"mfma_busy": 0.457, "file": "profiles/attn_patch_cog_mfma_counters.txt",
-                            "src": "a32e480031cb7edd"},
+                            "src": "e20cf9437eea5105"},
 }
 
 
