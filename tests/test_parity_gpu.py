@@ -124,6 +124,28 @@ def test_chunk_of_more_workgroups_than_one_grid_holds(torch, dtype):
     assert err <= TOL[dtype]["lse_rel"]
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_patch_of_more_workgroups_than_one_grid_holds(torch, dtype):
+    """The same for a patch step: every batch's fresh rows, buffer and output
+    are found in each of the launches (524 batches in the first)."""
+    B, H, d = 1100, 16000, 64
+    r = lambda *s: torch.randn(*s, device="cuda", dtype=torch.float32).to(tdtype(dtype))
+    q, fk, fv = r(B, 1, H, d), r(B, 1, H, d), r(B, 1, H, d)
+    kv = r(2, B, 2, H, d)
+    old = kv[:, :, 0].clone()
+    out = torch.full_like(q, float("nan"))
+    xd.xdit_patch_attn(q, kv, 1, 1, fk, fv, out)
+    assert torch.equal(kv[:, :, 0], old)
+    assert torch.equal(kv[0, :, 1:], fk) and torch.equal(kv[1, :, 1:], fv)
+    assert not out.isnan().any()
+    for b in (0, 523, 524, 1047, 1048, 1099):
+        k, v = kv[0, b].double(), kv[1, b].double()
+        w = torch.softmax((q[b].double() * k).sum(-1) / d ** 0.5, dim=0)
+        # two keys, |v| up to 5.5: the rounding of the weights and of the
+        # output, 2^-9 each in bf16, comes to 2 * 2^-9 * 5.5 = 2.2e-2 at most
+        check_out(to_np(out[b, 0]), (w[..., None] * v).sum(0).cpu().numpy(), dtype, f"batch {b}", scale=1.5)
+
+
 @pytest.mark.parametrize("d", [64, 72, 128])
 def test_constant_values_give_constant_output(torch, d):
     """Softmax rows sum to one: V rows all equal c gives O = c (up to the bf16
