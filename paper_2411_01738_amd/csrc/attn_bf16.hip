@@ -1347,17 +1347,32 @@ static int attn_kernel_choice() {
 //   * short sweeps, where the merge costs more than the waves give (24 heads,
 //     1000 queries; 1, 96, 160 and 256 keys): 6.9 / 7.8, 7.9 / 8.8, 8.9 / 9.5,
 //     10.6 / 10.1; split calls likewise (24 heads of 100 queries in 2 parts of
-//     96, 160 and 384 keys: 11.7 / 12.9, 12.6 / 13.4, 16.1 / 15.8).  The line is the two times'
-//     growth per tile.
+//     96, 160 and 384 keys: 11.7 / 12.9, 12.6 / 13.4, 16.1 / 15.8).  The line
+//     is the two times' growth per tile; a patch's is 0.25 us further (24
+//     heads, 1000 queries, 192 keys: patch 10.9 / 11.1, chunk 9.5 / 9.3).
 //   * one query tile per head on nearly all CUs: nothing shares its K/V, and
 //     the reads bound it (split calls of 24 heads of 64 queries: 8448 keys in
 //     240 parts 29.4 / 30.8; 48 heads 42.3 / 46.2, of 128 queries 44-46 / 46-47;
-//     with 192 parts 22.9 / 23.2; unsplit 200 heads of 65, 384 and
-//     1024 keys: 12.0 / 12.9, 22.8 / 21.4; 256 heads of 65, 1024 keys: 24.8 /
-//     26.9).
-static bool quad_ahead(int64_t workgroups, int64_t Nq, int64_t keys) {
+//     12 heads of 43 queries, 6164 keys in 192 parts 22.0 / 23.1, 8448 keys
+//     24.6 / 24.6; unsplit 200 heads of 65, 384 and 1024 keys: 12.0 / 12.9,
+//     22.8 / 21.4; 256 heads of 65, 1024 keys: 24.8 / 26.9).
+bool quad_ahead(int64_t workgroups, int64_t Nq, int64_t keys, bool patch) {
     const int64_t q = (keys + 31) / 32, w = (keys + 63) / 64;
-    return 0.53 * q < 0.82 * w + 0.6 || (Nq <= 128 && (workgroups > 224 || (workgroups > 192 && keys <= 512)));
+    return 0.53 * q < 0.82 * w + (patch ? 0.85 : 0.6) ||
+           (Nq <= 128 && (workgroups > 224 || (workgroups >= 192 && keys <= 512)));
+}
+
+// d = 128, 64-row tiles no more than CUs: whether a quad is ahead of strip.
+// Quad's time grows by 0.52 us per 32 keys and by 0.015 us per row of a tile,
+// strip's by 0.52 us per 64 keys; strip, whose merging waves are fewer, loses
+// more in ring steps, which read the running output, and in patches.  Measured, us for quad / strip, 24 heads: chunk 17
+// x 1 4.4 / 5.5, 17 x 160 6.2 / 6.5, 33 x 96 5.4 / 6.0, 33 x 128 5.9 / 5.9, 64 x
+// 96 6.0 / 6.2, 100 x 64 6.1 / 5.6; ring step 128 x 32 8.2 / 8.8, 100 x 64 8.6 /
+// 8.6, 128 x 128 9.6 / 9.0; patch 100 x 32 6.4 / 7.0, 64 x 96 7.2 / 7.7.
+bool quad_ahead_of_strip(int64_t Nq, int64_t Nk, bool patch, bool accum) {
+    const int64_t q = (Nk + 31) / 32, w = (Nk + 63) / 64;
+    const double r = Nq < 128 ? (double)Nq : 128.0;
+    return 0.52 * (q - w) + 0.015 * r < 1.5 + (accum ? 0.3 + 0.0045 * r : patch ? 0.3 : 0.0);
 }
 
 int64_t full_rounds(int64_t bh, int64_t Nq, int64_t rows) { return ((Nq + rows - 1) / rows * bh + kCUs - 1) / kCUs; }
@@ -1390,11 +1405,7 @@ Rounds rounds_cost(int D, int64_t bh, int64_t Nq, int64_t Nk) {
 //     heads, 300 x 4429: strip 24.5 us, narrow 27.3; 16 x 2500: 15.3 and 17.3;
 //     d = 72, 2 x 16 heads, 256 x 4096: 29.1 and 30.2; d = 128, 24 heads, 200 x
 //     4224: strip 48.0, wide 59.1; 100 x 500, 12 heads: 10.3 and 12.8), but
-//     for short sweeps at d = 128, where a quad's time grows by 0.52 us per 32
-//     keys and by 0.015 us per row of a tile, strip's by 0.52 us per 64 keys
-//     (24 heads, quad and strip: 17 x 1 4.4 and 5.5 us, 17 x 160 6.2 and 6.5,
-//     33 x 96 5.4 and 6.0, 33 x 128 5.9 both, 64 x 96 6.0 and 6.2, 100 x 64 6.1
-//     and 5.6).
+//     for what quad_ahead_of_strip says.
 //   * More: the cheapest by a model of the rounds, in units of a 128-key
 //     tile swept by a full round of quads (two per CU):
 //       quad: 1 per tile and full round, 0.58 when at most half of the
@@ -1413,15 +1424,13 @@ Rounds rounds_cost(int D, int64_t bh, int64_t Nq, int64_t Nk) {
 //         845 x 4429: 63 us, quad 74, wide 82; d = 72, 2 x 16 heads, 1500 x
 //         4096: 67, 79 and 87; the line: 845 x 500 14.0 and 13.8, 845 x 256
 //         10.5 and 8.9).
-Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk) {
+Shape pick_shape(int D, int64_t bh, int64_t Nq, int64_t Nk, bool patch, bool accum) {
     const int64_t n = (Nq + 127) / 128 * bh;
     const int64_t strip_rows = D > 96 ? 64 : 32;
-    if ((Nq + strip_rows - 1) / strip_rows * bh <= kCUs) {
-        const int64_t q = (Nk + 31) / 32, w = (Nk + 63) / 64, r = Nq < 128 ? Nq : 128;
-        return D > 96 && 0.52 * (q - w) + 0.015 * r < 1.5 ? kQuad : kStrip;
-    }
+    if ((Nq + strip_rows - 1) / strip_rows * bh <= kCUs)
+        return D > 96 && quad_ahead_of_strip(Nq, Nk, patch, accum) ? kQuad : kStrip;
     if (n <= kCUs) {
-        if (D > 96) return quad_ahead(n, Nq, Nk) ? kQuad : kWide;
+        if (D > 96) return quad_ahead(n, Nq, Nk, patch) ? kQuad : kWide;
         const int64_t narrow = (Nq + 63) / 64 * bh;
         const double qfill_w = (double)Nq / ((Nq + 127) / 128 * 128.0);
         const double qfill_n = (double)Nq / ((Nq + 63) / 64 * 64.0);
@@ -1454,9 +1463,10 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
             const int64_t keys = p.whole > 0 ? p.Nk : (int64_t)p.Nk * pairs / p.parts;  // of the longest sweep
             // more parts than 64-key tiles: wide leaves parts empty, which
             // the fix-up then skips (quad and wide: 15 heads, 128 x 528 in 16
-            // parts 21.1 and 17.5 us; 24 heads, 100 x 330 in 10 18.0 and 15.9)
-            const bool spare = p.parts > pairs * ((p.Nk + 63) / 64);
-            if (choice == 0 && (wgs > kCUs || (!spare && quad_ahead(wgs, p.Nq, keys))))
+            // parts 21.1 and 17.5 us; 24 heads, 100 x 330 in 10 18.0 and 15.9;
+            // but 3 heads, 78 x 228 in 6: 11.0 and 11.8)
+            const bool spare = p.parts > pairs * ((p.Nk + 63) / 64) && wgs > kCUs / 2;
+            if (choice == 0 && (wgs > kCUs || (!spare && quad_ahead(wgs, p.Nq, keys, PATCH))))
                 return launch<D, 4, 1, 32, PATCH>(p, s);
         }
         return launch<D, 4, 2, KW, PATCH>(p, s);
@@ -1464,7 +1474,7 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
     Shape shape = forced_shape();
     if (D > 96 ? shape == kNarrow || shape == kSix : D < 72 && shape == kOct) shape = kAuto;
     if (D > 96 && choice == 32) shape = kWide;
-    if (shape == kAuto) shape = pick_shape(D, (int64_t)p.B * p.H, p.Nq, p.Nk);
+    if (shape == kAuto) shape = pick_shape(D, (int64_t)p.B * p.H, p.Nq, p.Nk, PATCH, p.accum != 0);
     if constexpr (D <= 96) {
         if (shape == kNarrow) return launch<D, 2, 4, 32, PATCH>(p, s);
         if (shape == kSix) return launch<D, 6, 2, 32, PATCH>(p, s);
@@ -1481,7 +1491,7 @@ hipError_t dispatch(const AttnParams& p, hipStream_t s) {
 }  // namespace
 
 double unsplit_cost(int D, int64_t bh, int64_t Nq, int64_t Nk, double six_sweep) {
-    if (pick_shape(D, bh, Nq, Nk) != kSix) {
+    if (pick_shape(D, bh, Nq, Nk, false, false) != kSix) {
         const Rounds c = rounds_cost(D, bh, Nq, Nk);
         return 1.9 * (c.oct < c.quad ? c.oct : c.quad);
     }

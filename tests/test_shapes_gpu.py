@@ -89,28 +89,45 @@ def test_picked(d, H, nq, nk, shape):
     _chunk(torch, orc, 1, H, d, nq, nk, f"d={d} H={H} {nq} x {nk}", rows, shape)
 
 
-@pytest.mark.parametrize("H,nq,nk,splits,shape", [
-    (24, 17, 1, 1, "quad"), (24, 17, 160, 1, "quad"), (24, 17, 161, 1, "strip"), (24, 64, 96, 1, "quad"),
-    (24, 64, 97, 1, "strip"), (24, 100, 64, 1, "strip"),                                 # 64-row tiles fit the CUs
-    (24, 1000, 160, 1, "quad"), (24, 1000, 192, 1, "wide"), (24, 1000, 224, 1, "quad"), (24, 1000, 225, 1, "wide"),
-    (200, 65, 512, 1, "quad"), (200, 65, 513, 1, "wide"), (225, 65, 700, 1, "quad"),     # one tile per head
-    (24, 100, 448, 2, "quad"), (24, 100, 514, 2, "wide"), (15, 128, 528, 16, "wide"),    # split calls
-    (24, 64, 6144, 10, "quad"), (12, 64, 6144, 16, "wide")])
-def test_short_sweeps_at_128(H, nq, nk, splits, shape):
+@pytest.mark.parametrize("form,H,nq,nk,splits,shape", [
+    # 64-row tiles fit the CUs
+    ("chunk", 24, 17, 1, 1, "quad"), ("chunk", 24, 17, 160, 1, "quad"), ("chunk", 24, 17, 161, 1, "strip"),
+    ("chunk", 24, 64, 96, 1, "quad"), ("chunk", 24, 64, 97, 1, "strip"), ("chunk", 24, 100, 64, 1, "strip"),
+    ("ring", 24, 128, 32, 1, "quad"), ("ring", 24, 128, 33, 1, "strip"), ("ring", 24, 64, 160, 1, "quad"),
+    ("patch", 24, 64, 96, 1, "quad"), ("patch", 24, 64, 97, 1, "strip"), ("patch", 24, 128, 32, 1, "strip"),
+    # they do not, 128-row tiles do
+    ("chunk", 24, 1000, 160, 1, "quad"), ("chunk", 24, 1000, 192, 1, "wide"), ("chunk", 24, 1000, 224, 1, "quad"),
+    ("chunk", 24, 1000, 225, 1, "wide"), ("ring", 24, 1000, 192, 1, "wide"), ("patch", 24, 1000, 192, 1, "quad"),
+    ("patch", 24, 1000, 225, 1, "wide"),
+    # one tile per head
+    ("chunk", 192, 65, 512, 1, "quad"), ("chunk", 192, 65, 513, 1, "wide"), ("chunk", 191, 65, 512, 1, "wide"),
+    ("chunk", 225, 65, 700, 1, "quad"),
+    # split calls
+    ("chunk", 24, 100, 448, 2, "quad"), ("chunk", 24, 100, 514, 2, "wide"), ("chunk", 15, 128, 528, 16, "wide"),
+    ("chunk", 3, 78, 228, 6, "quad"), ("chunk", 24, 64, 6144, 10, "quad"), ("chunk", 12, 43, 6164, 16, "quad"),
+    ("ring", 12, 43, 8500, 16, "wide"), ("patch", 24, 100, 384, 2, "quad")])
+def test_short_sweeps_at_128(form, H, nq, nk, splits, shape):
     """Head dim 128, no more workgroups than CUs: 4-wave workgroups where the
     8-wave ones' merge, or the reads of K/V, cost more than they gain."""
     torch, orc, d = torch_mod(), oracle.get(), 128
-    print(f"[short] H={H} {nq} x {nk} in {splits}", flush=True)
+    print(f"[short] {form} H={H} {nq} x {nk} in {splits}", flush=True)
     q, k, v = (random_io((1, n, H, d), "bf16", 70 + n + i) for i, n in enumerate((nq, nk, nk)))
-    g = [to_gpu(x, "bf16") for x in (q, k, v)]
-    out = torch.full_like(g[0], float("nan"))
-    lse = torch.full((1, H, nq), float("nan"), device="cuda")
-    if splits > 1:
-        ws = torch.empty(xd.split_workspace_bytes(g[0], nk, splits), device="cuda", dtype=torch.uint8)
-        names = attention_kernels(lambda: xd.xdit_chunk_attn_split(*g, out, lse, splits, ws))
+    qg, kg, vg = (to_gpu(x, "bf16") for x in (q, k, v))
+    out = torch.full_like(qg, float("nan"))
+    lse = torch.full((1, H, nq), float("-inf"), device="cuda")  # ring: an empty state
+    ws = torch.empty(xd.split_workspace_bytes(qg, nk, splits), device="cuda", dtype=torch.uint8) if splits > 1 else None
+    if form == "patch":
+        a, n = nk // 3, nk // 2
+        kv = torch.stack([kg, vg])
+        fresh = kv[:, :, a:a + n].clone()
+        kv[:, :, a:a + n] = 0
+        f = lambda: xd.xdit_patch_attn_split(qg, kv, [(a, n)], fresh[0], fresh[1], out, lse, splits, ws)
     else:
-        names = attention_kernels(lambda: xd.xdit_chunk_attn(*g, out, lse))
-    assert names == [bf16_kernel(shape, d, parts=splits > 1)]
+        g = xd.xdit_chunk_attn_accum_split if form == "ring" else xd.xdit_chunk_attn_split
+        f = lambda: g(qg, kg, vg, out, lse, splits, ws)
+    assert attention_kernels(f) == [bf16_kernel(shape, d, patch=form == "patch", parts=splits > 1)]
+    if form == "patch":
+        assert torch.equal(kv[0], kg) and torch.equal(kv[1], vg)
     rows, heads = sample_rows(nq, 23, [0, nq - 1]), slice(0, 2)
     ro, rl = orc.attention(q[:, rows, heads].copy(), k[:, :, heads].copy(), v[:, :, heads].copy())
     check_out(to_np(out)[:, rows, heads], ro, "bf16", shape)
