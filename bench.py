@@ -50,13 +50,13 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E (published)
 # kernel build it was taken on (sha256 prefix of the sources and their compile
 # flags); a different build reports null.
 MEASURED_TRAFFIC = {
-    ("pixart", "patch_attn"): {"bytes": (49250 + 13878) * 1024, "src": "e20cf9437eea5105"},
-    ("sd3", "patch_attn"): {"bytes": (59113 + 9216) * 1024, "src": "e20cf9437eea5105"},
+    ("pixart", "patch_attn"): {"bytes": (49360 + 13875) * 1024, "src": "d8ead101225fc088"},
+    ("sd3", "patch_attn"): {"bytes": (59122 + 9216) * 1024, "src": "d8ead101225fc088"},
     # the partitioned sweep and its fix-up, one launch of each per call
-    ("flux", "chunk_attn"): {"bytes": (139889 + 41225) * 1024, "src": "e20cf9437eea5105"},
-    ("flux_ring", "chunk_attn"): {"bytes": (158721 + 41263) * 1024, "src": "e20cf9437eea5105"},
-    ("cog", "patch_attn"): {"bytes": (259244 + 19744) * 1024, "src": "e20cf9437eea5105"},
-    ("cog", "chunk_attn"): {"bytes": (133480 + 109990) * 1024, "src": "e20cf9437eea5105"},
+    ("flux", "chunk_attn"): {"bytes": (139997 + 41225) * 1024, "src": "d8ead101225fc088"},
+    ("flux_ring", "chunk_attn"): {"bytes": (158680 + 41275) * 1024, "src": "d8ead101225fc088"},
+    ("cog", "patch_attn"): {"bytes": (259259 + 19744) * 1024, "src": "d8ead101225fc088"},
+    ("cog", "chunk_attn"): {"bytes": (133422 + 109990) * 1024, "src": "d8ead101225fc088"},
 }
 
 
@@ -84,16 +84,16 @@ def traffic_of(workload: str, kind: str) -> dict:
 # summary file and the kernel build's fingerprint; a different build reports
 # nothing.
 MEASURED_COUNTERS = {
-    ("pixart", "patch_attn"): {"mfma_busy": 0.378, "file": "profiles/attn_patch_pixart_mfma_counters.txt",
-                               "src": "e20cf9437eea5105"},
+    ("pixart", "patch_attn"): {"mfma_busy": 0.379, "file": "profiles/attn_patch_pixart_mfma_counters.txt",
+                               "src": "d8ead101225fc088"},
     ("sd3", "patch_attn"): {"mfma_busy": 0.353, "file": "profiles/attn_patch_sd3_mfma_counters.txt",
-                            "src": "e20cf9437eea5105"},
+                            "src": "d8ead101225fc088"},
     ("flux", "chunk_attn"): {"mfma_busy": 0.531, "file": "profiles/attn_chunk_flux_mfma_counters.txt",
-                             "src": "e20cf9437eea5105"},
+                             "src": "d8ead101225fc088"},
     ("cog", "patch_attn"): {"mfma_busy": 0.406, "file": "profiles/attn_patch_cog_mfma_counters.txt",
-                            "src": "e20cf9437eea5105"},
+                            "src": "d8ead101225fc088"},
     ("cog", "chunk_attn"): {"mfma_busy": 0.457, "file": "profiles/attn_patch_cog_mfma_counters.txt",
-                            "src": "e20cf9437eea5105"},
+                            "src": "d8ead101225fc088"},
 }
 
 
